@@ -255,7 +255,9 @@ int sdp_projection_variant_kind(int32_t dtype, int32_t variant, int32_t *kind);
  * eigenvalue follows the scalar maps; the bound takes n - 1 eigenvalues at
  * the worst point of a fine grid).  FP32-eig's default tolerance 1e-6 gives
  * (12, 2) for n = 16; FP64's 1e-14 gives (29, 2).  Tolerances below 1e-16
- * are taken as 1e-16.  SDP_ERR_ARG if n < 1 or a pointer is NULL. */
+ * are taken as 1e-16.  This is the worst case over all spectra: the kernels
+ * stop earlier once ||I - X^2||_F shows every eigenvalue near +-1.
+ * SDP_ERR_ARG if n < 1 or a pointer is NULL. */
 int sdp_sign_schedule(double tol, int32_t n, int32_t *k1, int32_t *k2);
 
 /* The variant sdp_psd_project_batched runs for blocks of up to max_size

@@ -1627,6 +1627,61 @@ void sign_schedule(double tol, int n, int *k1_out, int *k2_out) {
   *k2_out = it->second.second;
 }
 
+// The plan the kernels run: sign_schedule's worst case, and for every count k
+// of fast steps after which ||I - X^2||_F <= SIGN_THETA was seen the
+// Newton-Schulz steps that finish the iteration after one more fast step.
+// There every eigenvalue satisfies |1 - x_k^2| <= SIGN_THETA, so only the
+// starting points x_0 of the grid whose scalar iterates do are left, and the
+// bound 2 sqrt(n - 1) max e <= tol of sign_schedule is taken over those.
+// (The first step scales X0 by c >= 1 with |c X0| <= SIGN_X_MAX: an eigenvalue
+// delta starts at x_0 = c delta, and |x_0| |1 - s| / 2 bounds its error.)
+SignPlan sign_plan(double tol, int n) {
+  static std::mutex mu;
+  static std::map<std::pair<double, int>, SignPlan> cache;
+  const double t = tol >= 1e-16 ? tol : 1e-16;
+  std::lock_guard<std::mutex> lock(mu);
+  const std::pair<double, int> key(t, n);
+  const auto it = cache.find(key);
+  if (it != cache.end()) return it->second;
+  SignPlan pl{};
+  sign_schedule(t, n, &pl.k1, &pl.k2);
+  const double target = t / (2.0 * std::sqrt((double)std::max(n - 1, 1)));
+  const int dec = std::max(1, (int)std::ceil(-std::log10(2.0 * target)));
+  std::vector<double> d;
+  for (int j = 0; j <= 256 * dec; ++j) d.push_back(std::pow(10.0, -dec + j / 256.0));
+  for (int j = 1; j <= 1024; ++j) d.push_back(SIGN_X_MAX * j / 1024.0);
+  const auto fast = [](double v) { return v * (3.0 - 3.2 * v * v + 1.2 * v * v * v * v); };
+  const auto newton = [](double v) { return v * (3.0 - v * v) / 2.0; };
+  // Newton-Schulz steps after which the starting points marked in `in` meet
+  // the bound from the iterates x (0 if not within `most`)
+  const auto steps = [&](std::vector<double> x, const std::vector<char> &in, int least, int most) {
+    for (int k2 = 1; k2 <= most; ++k2) {
+      double e = 0.0;
+      for (size_t j = 0; j < d.size(); ++j) {
+        x[j] = newton(x[j]);
+        if (in[j]) e = std::max(e, d[j] * std::fabs(1.0 - x[j]) / 2.0);
+      }
+      if (k2 >= least && e <= target) return k2;
+    }
+    return 0;
+  };
+  std::vector<double> x(d);
+  std::vector<char> in(d.size());
+  for (int k = 0; k < pl.k1; ++k) {   // x: after k fast steps
+    for (size_t j = 0; j < d.size(); ++j) in[j] = std::fabs(1.0 - x[j] * x[j]) <= SIGN_THETA;
+    for (double &v : x) v = fast(v);
+    if (k == 0 || k >= SignPlan::KMAX) continue;
+    const int n2 = steps(x, in, 1, 15);
+    if (n2 > 0 && 3 * (k + 1) + 2 * n2 < 3 * pl.k1 + 2 * pl.k2) pl.set_steps_after(k, n2);
+  }
+  // the worst case from the scaled start (x_0 up to SIGN_X_MAX)
+  std::fill(in.begin(), in.end(), 1);
+  const int n2 = steps(x, in, pl.k2, 12);
+  if (n2 > 0) pl.k2 = n2;
+  cache.emplace(key, pl);
+  return pl;
+}
+
 hipError_t launch_dual_update(const ProjArgs &a, int64_t ncl, hipStream_t st) {
   if (ncl <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_dual_update, dim3((unsigned)ncl), dim3(256), 0, st, a);
@@ -1720,141 +1775,210 @@ int projection_bucket(int precision, int s) {
 
 int projection_max_size(int precision) { return 128; }
 
-// The sign iteration for blocks of 16, one wave per block, entirely in
-// registers.  A 16 x 16 x 16 product is four 16x16x4 matrix-core steps; the
-// sum over k may be split over the steps in any order as long as both
-// operands agree, and step j takes k = R(g, j) from lane group g = l / 16,
-// where R(g, r) is the row of result register r (4g + r for FP32, g + 4r for
-// FP64).  Lane l then keeps X(R(g, r), l mod 16) in register r, and that is
-// exactly its operand of step r of the next product: the left operand
-// X(l mod 16, k) = X(k, l mod 16) by symmetry, the right one M(k, l mod 16).
-// So every product is four back-to-back steps on registers.  Using the
-// transposed element for the left operand makes each product X^T M, equal
-// to X M only while X is symmetric: without a correction the antisymmetric
-// rounding grows through the iteration (errors near 1e-2 in a lane-exact
-// simulation: the antisymmetric part changes sign and is scaled by up to 3
-// at every step), so X <- (X + X^T) / 2 through LDS after every second step
-// and after the last (the part then stays within 9 steps' rounding), and
+// The sign iteration for blocks of up to 16 TB vertices (TB = 1, 2), one wave
+// per block, entirely in registers.  A 16 x 16 x 16 product is four 16x16x4
+// matrix-core steps; the sum over k may be split over the steps in any order
+// as long as both operands agree, and step j takes k = R(g, j) from lane
+// group g = l / 16, where R(g, r) is the row of result register r (4g + r for
+// FP32, g + 4r for FP64).  Lane l then keeps X(16 I + R(g, r), 16 J + l mod 16)
+// in register r of tile t = TB I + J, and that is exactly its operand of step r
+// of the next product: the left operand of tile (I, J) at depth tile K,
+// X(16 I + i, 16 K + k), is by symmetry register j of tile (K, I), the right
+// one register j of tile (K, J).  So every product is 4 TB^3 back-to-back
+// steps on registers (for TB = 2 all four tiles are formed, both off-diagonal
+// ones included, since each is the other's operand).
+// Using the transposed element for the left operand makes each product X^T M,
+// equal to X M only while X is symmetric: without a correction the
+// antisymmetric rounding grows through the iteration (errors near 1e-2 in a
+// lane-exact simulation: the antisymmetric part changes sign and is scaled by
+// up to 3 at every step), so X <- (X + X^T) / 2 through LDS after every second
+// step and after the last (the part then stays within 9 steps' rounding), and
 // once more for the result.
 template <typename T>
 __device__ inline int sign16_row(int g, int r) {
   return sizeof(T) == 4 ? 4 * g + r : g + 4 * r;
 }
 
-template <typename T>
-__global__ __launch_bounds__(64) void k_project_sign16(const int32_t *__restrict__ sizes,
-                                                      const int64_t *__restrict__ offsets,
-                                                      const T *__restrict__ in,
-                                                      T *__restrict__ out, int k1, int k2) {
-  typedef typename Mma<T>::v4 v4;
-  __shared__ T C[16 * 17];
-  const int l = threadIdx.x, g = l >> 4, col = l & 15;
-  const int s = sizes[blockIdx.x];
-  const int64_t off = offsets[blockIdx.x];
-  if (s <= 0 || s > 16) return;   // sizes beyond max_size are left untouched
-  T w[4];
-  double f2 = 0.0;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = sign16_row<T>(g, r);
-    T v = T(0);
-    if (row < s && col < s)
-      v = T(0.5) * (in[off + (int64_t)row * s + col] + in[off + (int64_t)col * s + row]);
-    w[r] = v;
-    f2 += (double)v * (double)v;
-  }
-  f2 = wave_sum(f2);
-  if (!(f2 > 0.0 && f2 < INFINITY)) {
-    const T fill = f2 == 0.0 ? T(0) : T(NAN);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = sign16_row<T>(g, r);
-      if (row < s && col < s) out[off + (int64_t)row * s + col] = fill;
-    }
-    return;
-  }
-  const T scale = (T)(1.0 / sqrt(f2));
-  T x[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) x[r] = w[r] * scale;
-  // identity in the register layout
-  T id[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) id[r] = sign16_row<T>(g, r) == col ? T(1) : T(0);
-  const auto prod = [](const T (&a)[4], const T (&b)[4], T (&c)[4]) {
-    v4 acc = v4{0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc = Mma<T>::step(a[j], b[j], acc);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) c[r] = acc[r];
+// Sum over the wave, the same value in every lane: row rotations by DPP (each
+// row of 16 lanes), then the four rows through scalar registers.  (Six
+// shuffles through LDS would be a serial chain as long as a product.)
+__device__ inline float wave_total_f32(float v) {
+  const auto ror = [](float x, auto ctrl) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false));
   };
-  for (int it = 0; it < k1 + k2; ++it) {
-    T y[4], m[4];
-    prod(x, x, y);                                              // Y = X^2
-    if (it < k1) {
+  v += ror(v, std::integral_constant<int, 0x128>());   // row_ror:8
+  v += ror(v, std::integral_constant<int, 0x124>());   // row_ror:4
+  v += ror(v, std::integral_constant<int, 0x122>());   // row_ror:2
+  v += ror(v, std::integral_constant<int, 0x121>());   // row_ror:1
+  const int b = __float_as_int(v);
+  return (__int_as_float(__builtin_amdgcn_readlane(b, 0)) +
+          __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
+         (__int_as_float(__builtin_amdgcn_readlane(b, 32)) +
+          __int_as_float(__builtin_amdgcn_readlane(b, 48)));
+}
+
+// The scale of the first fast step: ||X^2||_F^(1/2) bounds the largest
+// eigenvalue of X0 = W / ||W||_F, which for a spectrum of n similar
+// eigenvalues is far below 1; X0 times c = SIGN_X_MAX / ||X0^2||_F^(1/2) still
+// lies in the basin of the fast step and its small eigenvalues start c times
+// nearer (half a step for blocks of 16, more than one for 128).
+__device__ inline float sign_scale(float y2) {
+  return y2 > 0.0f ? SIGN_X_MAX * rsqrtf(sqrtf(y2)) : 1.0f;   // (a NaN takes 1)
+}
+
+// One 16 TB x 16 TB product z = p^T q on registers (layout above).
+template <typename T, int TB>
+__device__ __forceinline__ void sign_prod(const T (&p)[TB * TB][4], const T (&q)[TB * TB][4],
+                                          T (&z)[TB * TB][4]) {
+  typedef typename Mma<T>::v4 v4;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m[r] = T(-3.2) * id[r] + T(1.2) * y[r];
-      T t[4];
-      prod(y, m, t);                                            // T = Y (-3.2 I + 1.2 Y)
+  for (int I = 0; I < TB; ++I)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m[r] = T(3) * id[r] + t[r];
-    } else {
+    for (int J = 0; J < TB; ++J) {
+      v4 acc = v4{0, 0, 0, 0};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m[r] = T(1.5) * id[r] - T(0.5) * y[r];
+      for (int K = 0; K < TB; ++K)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = Mma<T>::step(p[TB * K + I][j], q[TB * K + J][j], acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z[TB * I + J][r] = acc[r];
     }
-    T xn[4];
-    prod(x, m, xn);                                             // X <- X M
-    if ((it & 1) || it == k1 + k2 - 1) {
-      // X <- (X + X^T) / 2 (both triangles from the same two values)
+}
+
+// dst = (v + v^T) / 2 through C (both triangles from the same two values).
+template <typename T, int TB>
+__device__ __forceinline__ void sign_symmetrise(const T (&v)[TB * TB][4], T (&dst)[TB * TB][4],
+                                                T *C) {
+  constexpr int NTL = TB * TB, CP = 16 * TB + 1;
+  const int g = threadIdx.x >> 4, col = threadIdx.x & 15;
+  const auto rowof = [&](int t, int r) { return 16 * (t / TB) + sign16_row<T>(g, r); };
+  const auto colof = [&](int t) { return 16 * (t % TB) + col; };
 #pragma unroll
-      for (int r = 0; r < 4; ++r) C[sign16_row<T>(g, r) * 17 + col] = xn[r];
-      __syncthreads();
+  for (int t = 0; t < NTL; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) x[r] = T(0.5) * (xn[r] + C[col * 17 + sign16_row<T>(g, r)]);
-      __syncthreads();
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) x[r] = xn[r];
-    }
-  }
-  // W S, symmetrised through LDS: P+(W) = (W + (W S + S W) / 2) / 2
-  T c[4];
-  prod(w, x, c);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) C[sign16_row<T>(g, r) * 17 + col] = c[r];
+    for (int r = 0; r < 4; ++r) C[rowof(t, r) * CP + colof(t)] = v[t][r];
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = sign16_row<T>(g, r);
-    if (row < s && col < s)
-      out[off + (int64_t)row * s + col] = T(0.5) * (w[r] + T(0.5) * (c[r] + C[col * 17 + row]));
+  for (int t = 0; t < NTL; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) dst[t][r] = T(0.5) * (v[t][r] + C[colof(t) * CP + rowof(t, r)]);
+  __syncthreads();
+}
+
+// x <- sign(x) for x = W / ||W||_F of a block of s vertices (zero outside),
+// in at most pl.k1 fast and pl.k2 Newton-Schulz steps.  The squares Y = X^2
+// that every fast step forms tell how far the iteration is: once
+// ||I - Y||_F <= SIGN_THETA every eigenvalue is near +-1, and the Newton-Schulz
+// steps that remain are looked up (SignPlan).  The norm is formed beside the
+// two products that follow Y, so the test costs no latency; the step in
+// flight is finished.
+// Bound: the matrix cores (FP64: 64 cycles per 16x16x4 step), then the latency
+// of the chain of products, so their number is what counts.  On blocks with
+// independent N(0,1) entries it falls from 92 to about 25 (FP64, s = 16) and
+// from 41 to 22 (FP32).
+template <typename T, int TB>
+__device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const SignPlan &pl, T *C) {
+  constexpr int NTL = TB * TB;
+  const int g = threadIdx.x >> 4, col = threadIdx.x & 15;
+  T id[NTL][4];   // the identity on the block's own vertices
+#pragma unroll
+  for (int t = 0; t < NTL; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * (t / TB) + sign16_row<T>(g, r);
+      id[t][r] = (row == 16 * (t % TB) + col && row < s) ? T(1) : T(0);
+    }
+  int odd = 0, n2 = pl.k2;
+  for (int k = 0; k < pl.k1; ++k) {
+    T y[NTL][4], m[NTL][4], z[NTL][4];
+    sign_prod<T, TB>(x, x, y);                                  // Y = X^2
+    T c1 = T(1), c3 = T(1), c5 = T(1);
+    float e2 = INFINITY;
+    if (k == 0) {
+      float y2 = 0.0f;
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y2 += (float)y[t][r] * (float)y[t][r];
+      c1 = (T)sign_scale(wave_total_f32(y2));
+      c3 = c1 * c1 * c1;
+      c5 = c3 * c1 * c1;
+    } else {
+      e2 = 0.0f;
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float d = (float)(id[t][r] - y[t][r]);
+          e2 += d * d;
+        }
+      e2 = wave_total_f32(e2);
+    }
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        m[t][r] = (T(-3.2) * c3) * id[t][r] + (T(1.2) * c5) * y[t][r];
+    sign_prod<T, TB>(y, m, z);                                  // Z = Y (-3.2 I + 1.2 Y)
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m[t][r] = (T(3) * c1) * id[t][r] + z[t][r];
+    sign_prod<T, TB>(x, m, z);                                  // X <- X (3 I + Z)
+    if (odd) {
+      sign_symmetrise<T, TB>(z, x, C);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[t][r] = z[t][r];
+    }
+    odd ^= 1;
+    const int stop = pl.steps_after(k);
+    if (stop > 0 && e2 <= SIGN_THETA * SIGN_THETA) {
+      n2 = stop;
+      break;
+    }
+  }
+  for (int k = 0; k < n2; ++k) {
+    T y[NTL][4], m[NTL][4], z[NTL][4];
+    sign_prod<T, TB>(x, x, y);
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m[t][r] = T(1.5) * id[t][r] - T(0.5) * y[t][r];
+    sign_prod<T, TB>(x, m, z);                                  // X <- X (3 I - X^2) / 2
+    if (odd || k == n2 - 1) {
+      sign_symmetrise<T, TB>(z, x, C);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[t][r] = z[t][r];
+    }
+    odd ^= 1;
   }
 }
 
-// The same for blocks of 32, one wave per block: X is held as 2 x 2 tiles
-// of 16 (tile t = 2 I + J in registers 4t .. 4t + 3, rows 16 I + R(g, r),
-// column 16 J + l mod 16).  Tile (I, J) of a product sums over the depth
-// tiles K: its left operand X(16 I + i, 16 K + k) is, by symmetry, register
-// j of tile (K, I), its right operand register j of tile (K, J), so each
-// product is 32 matrix-core steps on registers (all four tiles are formed,
-// both off-diagonal ones included, since each is the other's operand).
-template <typename T>
-__global__ __launch_bounds__(64) void k_project_sign32(const int32_t *__restrict__ sizes,
-                                                      const int64_t *__restrict__ offsets,
-                                                      const T *__restrict__ in,
-                                                      T *__restrict__ out, int k1, int k2) {
-  typedef typename Mma<T>::v4 v4;
-  __shared__ T C[32 * 33];
+// Standalone projections of row-major blocks of up to 16 TB vertices.
+template <typename T, int TB>
+__global__ __launch_bounds__(64) void k_project_sign_regs(const int32_t *__restrict__ sizes,
+                                                          const int64_t *__restrict__ offsets,
+                                                          const T *__restrict__ in,
+                                                          T *__restrict__ out, SignPlan pl) {
+  constexpr int NTL = TB * TB, NB = 16 * TB;
+  __shared__ T C[NB * (NB + 1)];
   const int l = threadIdx.x, g = l >> 4, col = l & 15;
   const int s = sizes[blockIdx.x];
   const int64_t off = offsets[blockIdx.x];
-  if (s <= 0 || s > 32) return;   // sizes beyond max_size are left untouched
-  const auto rowof = [&](int t, int r) { return 16 * (t >> 1) + sign16_row<T>(g, r); };
-  const auto colof = [&](int t) { return 16 * (t & 1) + col; };
-  T w[4][4];
+  if (s <= 0 || s > NB) return;   // sizes beyond max_size are left untouched
+  const auto rowof = [&](int t, int r) { return 16 * (t / TB) + sign16_row<T>(g, r); };
+  const auto colof = [&](int t) { return 16 * (t % TB) + col; };
+  T w[NTL][4];
   double f2 = 0.0;
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int t = 0; t < NTL; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = rowof(t, r), cc = colof(t);
@@ -1868,7 +1992,7 @@ __global__ __launch_bounds__(64) void k_project_sign32(const int32_t *__restrict
   if (!(f2 > 0.0 && f2 < INFINITY)) {
     const T fill = f2 == 0.0 ? T(0) : T(NAN);
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < NTL; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = rowof(t, r), cc = colof(t);
@@ -1877,77 +2001,18 @@ __global__ __launch_bounds__(64) void k_project_sign32(const int32_t *__restrict
     return;
   }
   const T scale = (T)(1.0 / sqrt(f2));
-  T x[4][4], id[4][4];
+  T x[NTL][4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int t = 0; t < NTL; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      x[t][r] = w[t][r] * scale;
-      id[t][r] = rowof(t, r) == colof(t) ? T(1) : T(0);
-    }
-  const auto prod = [](const T (&a)[4][4], const T (&b)[4][4], T (&c)[4][4]) {
-#pragma unroll
-    for (int I = 0; I < 2; ++I)
-#pragma unroll
-      for (int J = 0; J < 2; ++J) {
-        v4 acc = v4{0, 0, 0, 0};
-#pragma unroll
-        for (int K = 0; K < 2; ++K)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc = Mma<T>::step(a[2 * K + I][j], b[2 * K + J][j], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) c[2 * I + J][r] = acc[r];
-      }
-  };
-  const auto symmetrise = [&](const T (&v)[4][4], T (&dst)[4][4]) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) C[rowof(t, r) * 33 + colof(t)] = v[t][r];
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) dst[t][r] = T(0.5) * (v[t][r] + C[colof(t) * 33 + rowof(t, r)]);
-    __syncthreads();
-  };
-  for (int it = 0; it < k1 + k2; ++it) {
-    T y[4][4], m[4][4];
-    prod(x, x, y);                                              // Y = X^2
-    if (it < k1) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = T(-3.2) * id[t][r] + T(1.2) * y[t][r];
-      T u[4][4];
-      prod(y, m, u);                                            // U = Y (-3.2 I + 1.2 Y)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = T(3) * id[t][r] + u[t][r];
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = T(1.5) * id[t][r] - T(0.5) * y[t][r];
-    }
-    T xn[4][4];
-    prod(x, m, xn);                                             // X <- X M
-    if ((it & 1) || it == k1 + k2 - 1) {
-      symmetrise(xn, x);
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[t][r] = xn[t][r];
-    }
-  }
+    for (int r = 0; r < 4; ++r) x[t][r] = w[t][r] * scale;
+  sign_iterate<T, TB>(x, s, pl, C);
   // W S, symmetrised: P+(W) = (W + (W S + S W) / 2) / 2
-  T c[4][4], cs[4][4];
-  prod(w, x, c);
-  symmetrise(c, cs);
+  T c[NTL][4], cs[NTL][4];
+  sign_prod<T, TB>(w, x, c);
+  sign_symmetrise<T, TB>(c, cs, C);
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int t = 0; t < NTL; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = rowof(t, r), cc = colof(t);
@@ -1958,7 +2023,7 @@ __global__ __launch_bounds__(64) void k_project_sign32(const int32_t *__restrict
 // ---------------------------------------------------------------------------
 // Algorithm 1's clique step for blocks of up to 16 TB vertices (TB = 1, 2) in
 // one wave's registers, with no eigenvectors: X_k = P+(W_k) by the sign
-// iteration of k_project_sign16/32 on W_k = H_k x - Lambda_k / rho, then the
+// iteration (sign_iterate) on W_k = H_k x - Lambda_k / rho, then the
 // multiplier update Lambda_k += rho (X_k - H_k x) (XkUpdate, LambdakUpdate)
 // and the five residual partials of k_project's ADMM epilogue.  With DUAL,
 // Algorithm 2's z-update instead: z_k = P+(v_k - lambda_k / rho) (zkUpdate)
@@ -1972,11 +2037,10 @@ __global__ __launch_bounds__(64) void k_project_sign32(const int32_t *__restrict
 // ---------------------------------------------------------------------------
 template <typename T, int TB, bool DUAL, bool HSDE = false>
 __global__ __launch_bounds__(64) void k_admm_sign(ProjArgs a, const int32_t *__restrict__ list,
-                                                  int k1, int k2) {
+                                                  SignPlan pl) {
   static_assert(!(DUAL && HSDE), "one algorithm per kernel");
-  constexpr int NTL = TB * TB, NB = 16 * TB, CP = NB + 1;
-  typedef typename Mma<T>::v4 v4;
-  __shared__ T C[NB * CP];
+  constexpr int NTL = TB * TB, NB = 16 * TB;
+  __shared__ T C[NB * (NB + 1)];
   const int l = threadIdx.x, g = l >> 4, col = l & 15;
   // neighbouring cliques share coordinates of u: keep them on one XCD
   const int nb = gridDim.x, q8 = nb / 8, r8 = nb % 8, x8 = blockIdx.x % 8;
@@ -2047,76 +2111,16 @@ __global__ __launch_bounds__(64) void k_admm_sign(ProjArgs a, const int32_t *__r
 
   // sign(W) from X0 = W / ||W||_F (W = 0 gives X = 0 and P+(W) = 0)
   const T scale = f2 > 0.0 ? (T)(1.0 / sqrt(f2)) : T(0);
-  T x[NTL][4], id[NTL][4];
+  T x[NTL][4];
 #pragma unroll
   for (int t = 0; t < NTL; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      x[t][r] = w[t][r] * scale;
-      id[t][r] = rowof(t, r) == colof(t) ? T(1) : T(0);
-    }
-  const auto prod = [](const T (&p)[NTL][4], const T (&q)[NTL][4], T (&z)[NTL][4]) {
-#pragma unroll
-    for (int I = 0; I < TB; ++I)
-#pragma unroll
-      for (int J = 0; J < TB; ++J) {
-        v4 acc = v4{0, 0, 0, 0};
-#pragma unroll
-        for (int K = 0; K < TB; ++K)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc = Mma<T>::step(p[TB * K + I][j], q[TB * K + J][j], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) z[TB * I + J][r] = acc[r];
-      }
-  };
-  const auto symmetrise = [&](const T (&v)[NTL][4], T (&dst)[NTL][4]) {
-#pragma unroll
-    for (int t = 0; t < NTL; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) C[rowof(t, r) * CP + colof(t)] = v[t][r];
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NTL; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) dst[t][r] = T(0.5) * (v[t][r] + C[colof(t) * CP + rowof(t, r)]);
-    __syncthreads();
-  };
-  for (int it = 0; it < k1 + k2; ++it) {
-    T y[NTL][4], m[NTL][4];
-    prod(x, x, y);                                              // Y = X^2
-    if (it < k1) {
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = T(-3.2) * id[t][r] + T(1.2) * y[t][r];
-      T z[NTL][4];
-      prod(y, m, z);                                            // Z = Y (-3.2 I + 1.2 Y)
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = T(3) * id[t][r] + z[t][r];
-    } else {
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = T(1.5) * id[t][r] - T(0.5) * y[t][r];
-    }
-    T xn[NTL][4];
-    prod(x, m, xn);                                             // X <- X M
-    if ((it & 1) || it == k1 + k2 - 1) {
-      symmetrise(xn, x);
-    } else {
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[t][r] = xn[t][r];
-    }
-  }
+    for (int r = 0; r < 4; ++r) x[t][r] = w[t][r] * scale;
+  if (f2 != 0.0) sign_iterate<T, TB>(x, s, pl, C);   // (uniform)
   // X_k = P+(W) = (W + (W S + S W) / 2) / 2
   T c[NTL][4], cs[NTL][4];
-  prod(w, x, c);
-  symmetrise(c, cs);
+  sign_prod<T, TB>(w, x, c);
+  sign_symmetrise<T, TB>(c, cs, C);
 
   // epilogue on the lower entries: X_k, Lambda_k and the residual partials
   // (||X - Hx||^2, ||X||^2, ||Hx||^2, ||X - X_prev||^2, ||Lambda||^2, full
@@ -2238,10 +2242,13 @@ __global__ __launch_bounds__(64) void k_admm_sign(ProjArgs a, const int32_t *__r
 // under a branch of its own), and the accumulators live only inside the
 // pass.  The loads of step s + 1 are issued before the steps of s; the
 // scheduling barrier keeps the compiler from hoisting all of them, which
-// would need more registers than a wave has.
+// would need more registers than a wave has.  With fred (only as L <- L M, no
+// transform), the wave also leaves its share of ||e I - L M||_F^2 (e I on the
+// first s vertices) in fred[wave], which every wave may read after the pass.
 template <typename T, int N, int NTL>
 __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from_l, T alpha,
-                                        T beta, T sa, T sb, int J, int g, int c) {
+                                        T beta, T sa, T sb, int J, int g, int c, float *fred,
+                                        T e, int s) {
   constexpr int P = N + 1, STEPS = N / 4;
   typedef typename Mma<T>::v4 v4;
   const int jc = 16 * J + c;
@@ -2276,6 +2283,19 @@ __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from
       for (int t = 0; t < NTL; ++t) av[t] = an[t];
       b = bn;
     }
+  }
+  if (fred) {   // (uniform)
+    float q = 0.0f;
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * (J + t) + sign16_row<T>(g, r);
+        const float d = (float)((i == jc && i < s ? e : T(0)) - acc[t][r]);
+        if (i >= jc) q += (i == jc ? 1.0f : 2.0f) * d * d;
+      }
+    q = wave_total_f32(q);
+    if ((threadIdx.x & 63) == 0) fred[threadIdx.x >> 6] = q;
   }
   __syncthreads();   // every wave has read L
 #pragma unroll
@@ -2317,11 +2337,12 @@ __global__ __launch_bounds__(4 * N) void k_sign_big(ProjArgs a, const int32_t *_
                                                     const int32_t *__restrict__ sizes,
                                                     const int64_t *__restrict__ offsets,
                                                     const T *__restrict__ in, T *__restrict__ out,
-                                                    int k1, int k2) {
+                                                    SignPlan pl) {
   constexpr int P = N + 1, TN = N / 16, NT = 4 * N;
   static_assert(N % 16 == 0 && N >= 48 && N <= 128, "column blocks of 16");
   __shared__ T L[N * P];
   __shared__ double red[6 * (NT / 64)];
+  __shared__ float fred[NT / 64];
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, g = l >> 4, c = l & 15;
   const int J = (TN == 8 && w >= 4) ? 11 - w : w, nt = TN - J, jc = 16 * J + c;
 
@@ -2454,45 +2475,75 @@ __global__ __launch_bounds__(4 * N) void k_sign_big(ProjArgs a, const int32_t *_
 
   const int ntu = __builtin_amdgcn_readfirstlane(nt);   // uniform per wave
   // one pass: L <- sa I + sb (L M), M from x or alpha I + beta L (from_l)
-  const auto pass = [&](bool from_l, T alpha, T beta, T sa, T sb, int gq, int cq) {
+  const auto pass = [&](bool from_l, T alpha, T beta, T sa, T sb, int gq, int cq, float *fr, T e) {
     switch (ntu) {
-      case 8: if constexpr (TN >= 8) sb_pass<T, N, 8>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
-      case 7: if constexpr (TN >= 7) sb_pass<T, N, 7>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
-      case 6: if constexpr (TN >= 6) sb_pass<T, N, 6>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
-      case 5: if constexpr (TN >= 5) sb_pass<T, N, 5>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
-      case 4: if constexpr (TN >= 4) sb_pass<T, N, 4>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
-      case 3: sb_pass<T, N, 3>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
-      case 2: sb_pass<T, N, 2>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
-      default: sb_pass<T, N, 1>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq); break;
+      case 8: if constexpr (TN >= 8) sb_pass<T, N, 8>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      case 7: if constexpr (TN >= 7) sb_pass<T, N, 7>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      case 6: if constexpr (TN >= 6) sb_pass<T, N, 6>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      case 5: if constexpr (TN >= 5) sb_pass<T, N, 5>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      case 4: if constexpr (TN >= 4) sb_pass<T, N, 4>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      case 3: sb_pass<T, N, 3>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      case 2: sb_pass<T, N, 2>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      default: sb_pass<T, N, 1>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
     }
   };
-  // The passes of the k1 fast steps (L = X X; L = 3 I + L (-3.2 I + 1.2 L);
-  // L = L X, then x = L) and of the k2 Newton-Schulz steps (L = 1.5 I -
+  // The passes of the fast steps (L = X X; L = 3 I + L (-3.2 I + 1.2 L);
+  // L = L X, then x = L) and of the Newton-Schulz steps (L = 1.5 I -
   // 0.5 X X; L = L X, then x = L), and a last one, L = S W with W again in
-  // x.  (The lane index passes through an empty asm statement at each pass,
-  // so that the LDS addresses derived from it are formed in the pass instead
-  // of hoisted out of the loop and kept live, which spills.)
-  const int nprod = 3 * k1 + 2 * k2;
-  for (int q = 0; q <= nprod; ++q) {
+  // x.  As in sign_iterate, the norm of I - X X that the first pass of a fast
+  // step leaves in LDS ends the fast steps early (the step is finished), and
+  // the first one is scaled.  (The lane index passes through an empty asm
+  // statement at each pass, so that the LDS addresses derived from it are
+  // formed in the pass instead of hoisted out of the loop and kept live,
+  // which spills.)
+  // Bound: a workgroup per clique, by the matrix cores of its one compute
+  // unit (67% of their FP64 peak for N = 128), so the number of passes counts.
+  int k = 0, n2 = pl.k2, ph = f2 == 0.0 ? 4 : pl.k1 > 0 ? 0 : 3;
+  T c1 = T(1), c3 = T(1), c5 = T(1);
+  bool last_fast = false;
+  // ph: 0 Y, 1 Z, 2 X of a fast step; 3 Y, 5 X of a Newton-Schulz step; 4 S W
+  for (;;) {
     int lq = l;
     asm volatile("" : "+v"(lq));
     const int gq = lq >> 4, cq = lq & 15;
-    const bool fast = q < 3 * k1;
-    const int ph = fast ? q % 3 : ((q - 3 * k1) % 2 == 0 ? 0 : 2);   // Y, Z, X
-    if (q == nprod) gather_w();
+    if (ph == 4) gather_w();
     T sa = T(0), sb = T(1);
-    if (q < nprod && ph == 1) sa = T(3);
-    if (q < nprod && !fast && ph == 0) {
+    if (ph == 1) sa = T(3) * c1;
+    if (ph == 3) {
       sa = T(1.5);
       sb = T(-0.5);
     }
-    pass(q < nprod && ph == 1, T(-3.2), T(1.2), sa, sb, gq, cq);
-    if (q < nprod && ph == 2) {
+    pass(ph == 1, T(-3.2) * c3, T(1.2) * c5, sa, sb, gq, cq, ph == 0 ? fred : nullptr,
+         k == 0 ? T(0) : T(1));
+    if (ph == 4) break;
+    if (ph == 2 || ph == 5) {
 #pragma unroll
       for (int K = 0; K < TN; ++K)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           x[K][r] = L[(16 * K + sign16_row<T>(gq, r)) * P + 16 * J + cq];
+    }
+    if (ph == 0) {
+      float e2 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NT / 64; ++i) e2 += fred[i];
+      c1 = k == 0 ? (T)sign_scale(e2) : T(1);
+      c3 = c1 * c1 * c1;
+      c5 = c3 * c1 * c1;
+      const int stop = pl.steps_after(k);
+      last_fast = k > 0 && stop > 0 && e2 <= SIGN_THETA * SIGN_THETA;
+      if (last_fast) n2 = stop;
+      ++k;
+      last_fast = __builtin_amdgcn_readfirstlane(last_fast || k == pl.k1);
+      ph = 1;
+    } else if (ph == 1) {
+      ph = 2;
+    } else if (ph == 2) {
+      ph = !last_fast ? 0 : n2 > 0 ? 3 : 4;
+    } else if (ph == 3) {
+      ph = 5;
+    } else {
+      ph = --n2 > 0 ? 3 : 4;
     }
   }
 
@@ -2926,34 +2977,32 @@ hipError_t launch_sign(int count, const int32_t *sizes, const int64_t *offsets, 
 }
 
 hipError_t dispatch_sign(int dtype, int N, int NT, int count, const int32_t *sizes,
-                         const int64_t *offsets, const void *in, void *out, int k1, int k2,
+                         const int64_t *offsets, const void *in, void *out, const SignPlan &pl,
                          hipStream_t st) {
 #define SDP_SIGN(T, n, nt)                                                                     \
-  if (N == n && NT == nt) return launch_sign<T, n, nt>(count, sizes, offsets, in, out, k1, k2, st);
-  if (N == 16 && NT == 64) {   // blocks of 16: the register-resident kernel
-    if (dtype == 1)
-      hipLaunchKernelGGL(k_project_sign16<float>, dim3(count), dim3(64), 0, st, sizes, offsets,
-                         (const float *)in, (float *)out, k1, k2);
-    else
-      hipLaunchKernelGGL(k_project_sign16<double>, dim3(count), dim3(64), 0, st, sizes, offsets,
-                         (const double *)in, (double *)out, k1, k2);
-    return hipGetLastError();
+  if (N == n && NT == nt)                                                                      \
+    return launch_sign<T, n, nt>(count, sizes, offsets, in, out, pl.k1, pl.k2, st);
+  // blocks of 16 and 32: the register-resident kernels
+#define SDP_SIGN_REGS(T, n)                                                                    \
+  if (N == n && NT == 64) {                                                                    \
+    hipLaunchKernelGGL((k_project_sign_regs<T, n / 16>), dim3(count), dim3(64), 0, st, sizes,  \
+                       offsets, (const T *)in, (T *)out, pl);                                  \
+    return hipGetLastError();                                                                  \
   }
-  if (N == 32 && NT == 64) {   // blocks of 32: the register-resident kernel
-    if (dtype == 1)
-      hipLaunchKernelGGL(k_project_sign32<float>, dim3(count), dim3(64), 0, st, sizes, offsets,
-                         (const float *)in, (float *)out, k1, k2);
-    else
-      hipLaunchKernelGGL(k_project_sign32<double>, dim3(count), dim3(64), 0, st, sizes, offsets,
-                         (const double *)in, (double *)out, k1, k2);
-    return hipGetLastError();
+  if (dtype == 1) {
+    SDP_SIGN_REGS(float, 16)
+    SDP_SIGN_REGS(float, 32)
+  } else {
+    SDP_SIGN_REGS(double, 16)
+    SDP_SIGN_REGS(double, 32)
   }
+#undef SDP_SIGN_REGS
   // blocks of 48 and more: one block in LDS, the other operand in registers
   // (1.1-1.5x the rate of the two-block LDS kernel on 4096 blocks)
 #define SDP_SIGN_BIG(T, n)                                                                     \
   if (N == n && NT == 4 * n) {                                                                 \
     hipLaunchKernelGGL((k_sign_big<T, n, 0>), dim3(count), dim3(4 * n), 0, st, ProjArgs{},     \
-                       nullptr, sizes, offsets, (const T *)in, (T *)out, k1, k2);              \
+                       nullptr, sizes, offsets, (const T *)in, (T *)out, pl);                  \
     return hipGetLastError();                                                                  \
   }
   if (dtype == 1) {
@@ -3001,18 +3050,15 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
     // V, theta) gets the Jacobi default of the same block size
     if (!a.eig && NT == 64 && (N == 16 || N == 32)) {
       if (count <= 0) return hipSuccess;
-      int k1, k2;
-      sign_schedule(a.tol, N, &k1, &k2);
+      const SignPlan pl = sign_plan(a.tol, N);
 #define SDP_ADMM_SIGN(T, tb)                                                                    \
   if (a.hsde)                                                                                   \
     hipLaunchKernelGGL((k_admm_sign<T, tb, false, true>), dim3(count), dim3(64), 0, st, a, list, \
-                       k1, k2);                                                                 \
+                       pl);                                                                     \
   else if (a.dual)                                                                              \
-    hipLaunchKernelGGL((k_admm_sign<T, tb, true>), dim3(count), dim3(64), 0, st, a, list, k1,    \
-                       k2);                                                                     \
+    hipLaunchKernelGGL((k_admm_sign<T, tb, true>), dim3(count), dim3(64), 0, st, a, list, pl);   \
   else                                                                                          \
-    hipLaunchKernelGGL((k_admm_sign<T, tb, false>), dim3(count), dim3(64), 0, st, a, list, k1,   \
-                       k2);
+    hipLaunchKernelGGL((k_admm_sign<T, tb, false>), dim3(count), dim3(64), 0, st, a, list, pl);
       if (precision == 1) {
         if (N == 16) {
           SDP_ADMM_SIGN(float, 1)
@@ -3034,15 +3080,14 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
     // plan refuses the unrolled iterations for them)
     if (precision == 0 && N >= 48 && NT == 4 * N && !a.eig) {
       if (count <= 0) return hipSuccess;
-      int k1, k2;
-      sign_schedule(a.tol, N, &k1, &k2);
+      const SignPlan pl = sign_plan(a.tol, N);
       if (split_ws && split_workspace(precision, variant, count) > 0) {
         const int mode = a.hsde ? 3 : a.dual ? 2 : 1;
 #define SDP_SPLIT(n)                                                                           \
   if (N == n) {                                                                                \
-    if (mode == 3) return launch_split<n, 3>(a, list, count, split_ws, k1, k2, st);            \
-    if (mode == 2) return launch_split<n, 2>(a, list, count, split_ws, k1, k2, st);            \
-    return launch_split<n, 1>(a, list, count, split_ws, k1, k2, st);                           \
+    if (mode == 3) return launch_split<n, 3>(a, list, count, split_ws, pl.k1, pl.k2, st);      \
+    if (mode == 2) return launch_split<n, 2>(a, list, count, split_ws, pl.k1, pl.k2, st);      \
+    return launch_split<n, 1>(a, list, count, split_ws, pl.k1, pl.k2, st);                     \
   }
         SDP_SPLIT(96)
         SDP_SPLIT(128)
@@ -3053,13 +3098,13 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
   if (N == n) {                                                                                \
     if (a.hsde)                                                                                \
       hipLaunchKernelGGL((k_sign_big<double, n, 3>), dim3(count), dim3(4 * n), 0, st, a, list,  \
-                         nullptr, nullptr, nullptr, nullptr, k1, k2);                          \
+                         nullptr, nullptr, nullptr, nullptr, pl);                              \
     else if (a.dual)                                                                           \
       hipLaunchKernelGGL((k_sign_big<double, n, 2>), dim3(count), dim3(4 * n), 0, st, a, list,  \
-                         nullptr, nullptr, nullptr, nullptr, k1, k2);                          \
+                         nullptr, nullptr, nullptr, nullptr, pl);                              \
     else                                                                                       \
       hipLaunchKernelGGL((k_sign_big<double, n, 1>), dim3(count), dim3(4 * n), 0, st, a, list,  \
-                         nullptr, nullptr, nullptr, nullptr, k1, k2);                          \
+                         nullptr, nullptr, nullptr, nullptr, pl);                              \
     return hipGetLastError();                                                                  \
   }
       SDP_ADMM_BIG(48)
@@ -3097,9 +3142,7 @@ hipError_t launch_standalone_projection(int dtype, int variant, int count, const
   projection_variant_info(dtype, variant, &N, &NT);
   if (projection_variant_kind(dtype, variant) == 2) {
     if (count <= 0) return hipSuccess;
-    int k1, k2;
-    sign_schedule(tol, N, &k1, &k2);
-    return dispatch_sign(dtype, N, NT, count, sizes, offsets, in, out, k1, k2, st);
+    return dispatch_sign(dtype, N, NT, count, sizes, offsets, in, out, sign_plan(tol, N), st);
   }
   const int blk = projection_variant_two_level(dtype, variant);
   if (dtype == 1)

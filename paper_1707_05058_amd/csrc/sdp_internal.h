@@ -132,6 +132,23 @@ int projection_default_variant(int precision, int s);   // -1 if s is too large 
 // relative to ||W||_F: k1 fast steps, k2 Newton-Schulz steps (cached per
 // (tol, n); thread-safe)
 void sign_schedule(double tol, int n, int *k1, int *k2);
+// What the sign-function kernels run (sign_plan): at most k1 fast and k2
+// Newton-Schulz steps; and, for an iteration that has come near +-1 after k
+// fast steps, the Newton-Schulz steps left after one more fast step.
+constexpr float SIGN_THETA = 0.9f;    // ||I - X^2||_F that counts as near
+constexpr float SIGN_X_MAX = 1.25f;   // bound of the scaled start (the fast map's basin ends at 1.29)
+struct SignPlan {
+  static constexpr int KMAX = 32;
+  int32_t k1, k2;
+  uint64_t lo, hi;                    // 4 bits per k; 0: go on
+  // (two words and a select: an array indexed at run time would be copied to
+  // scratch memory)
+  __host__ __device__ int steps_after(int k) const {
+    return k < KMAX ? (int)((k < 16 ? lo : hi) >> (4 * (k & 15)) & 15) : 0;
+  }
+  void set_steps_after(int k, int n) { (k < 16 ? lo : hi) |= (uint64_t)n << (4 * (k & 15)); }
+};
+SignPlan sign_plan(double tol, int n);   // cached per (tol, n); thread-safe
 int projection_standalone_variant(int precision, int s);  // sign function where built
 hipError_t fill_random_blocks(int precision, void *out, int s, int count, uint32_t seed,
                               double offdiag, hipStream_t st);
