@@ -1889,44 +1889,59 @@ __device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const Si
       const int row = 16 * (t / TB) + sign16_row<T>(g, r);
       id[t][r] = (row == 16 * (t % TB) + col && row < s) ? T(1) : T(0);
     }
-  int odd = 0, n2 = pl.k2;
-  for (int k = 0; k < pl.k1; ++k) {
+  // one loop body for both kinds of step (a wave runs it for the first time
+  // on every launch, and its instructions come from memory then: with a loop
+  // each the projection of 2000 FP32 blocks of 16 took 13.4 us instead of 12.3)
+  int k = 0, k1 = pl.k1, n2 = pl.k2;   // fast steps done and allowed; steps left after them
+  T a1 = T(3), a3 = T(-3.2), a5 = T(1.2);
+  for (int it = 0;; ++it) {
     T y[NTL][4], m[NTL][4], z[NTL][4];
     sign_prod<T, TB>(x, x, y);                                  // Y = X^2
-    T c1 = T(1), c3 = T(1), c5 = T(1);
-    float e2 = INFINITY;
-    if (k == 0) {
-      float y2 = 0.0f;
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) y2 += (float)y[t][r] * (float)y[t][r];
-      c1 = (T)sign_scale(wave_total_f32(y2));
-      c3 = c1 * c1 * c1;
-      c5 = c3 * c1 * c1;
-    } else {
-      e2 = 0.0f;
+    bool last = false;
+    if (k < k1) {
+      const T one = k == 0 ? T(0) : T(1);
+      T d2 = T(0);
 #pragma unroll
       for (int t = 0; t < NTL; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float d = (float)(id[t][r] - y[t][r]);
-          e2 += d * d;
+          const T d = one * id[t][r] - y[t][r];
+          d2 += d * d;
         }
-      e2 = wave_total_f32(e2);
+      const float e2 = wave_total_f32((float)d2);
+      if (k == 0) {
+        const T c = (T)sign_scale(e2);
+        a1 *= c;
+        a3 *= c * c * c;
+        a5 *= c * c * c * c * c;
+      }
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[t][r] = a3 * id[t][r] + a5 * y[t][r];
+      sign_prod<T, TB>(y, m, z);                                // Z = Y (-3.2 I + 1.2 Y)
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[t][r] = a1 * id[t][r] + z[t][r];   // 3 I + Z
+      a1 = T(3);
+      a3 = T(-3.2);
+      a5 = T(1.2);
+      const int stop = pl.steps_after(k);   // (0 for k = 0)
+      ++k;
+      if (stop > 0 && e2 <= SIGN_THETA * SIGN_THETA) {
+        k1 = k;
+        n2 = stop;
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[t][r] = T(1.5) * id[t][r] - T(0.5) * y[t][r];
+      last = --n2 == 0;
     }
-#pragma unroll
-    for (int t = 0; t < NTL; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        m[t][r] = (T(-3.2) * c3) * id[t][r] + (T(1.2) * c5) * y[t][r];
-    sign_prod<T, TB>(y, m, z);                                  // Z = Y (-3.2 I + 1.2 Y)
-#pragma unroll
-    for (int t = 0; t < NTL; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) m[t][r] = (T(3) * c1) * id[t][r] + z[t][r];
-    sign_prod<T, TB>(x, m, z);                                  // X <- X (3 I + Z)
-    if (odd) {
+    sign_prod<T, TB>(x, m, z);   // X <- X (3 I + Z) or X (3 I - X^2) / 2
+    if ((it & 1) || last) {
       sign_symmetrise<T, TB>(z, x, C);
     } else {
 #pragma unroll
@@ -1934,30 +1949,7 @@ __device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const Si
 #pragma unroll
         for (int r = 0; r < 4; ++r) x[t][r] = z[t][r];
     }
-    odd ^= 1;
-    const int stop = pl.steps_after(k);
-    if (stop > 0 && e2 <= SIGN_THETA * SIGN_THETA) {
-      n2 = stop;
-      break;
-    }
-  }
-  for (int k = 0; k < n2; ++k) {
-    T y[NTL][4], m[NTL][4], z[NTL][4];
-    sign_prod<T, TB>(x, x, y);
-#pragma unroll
-    for (int t = 0; t < NTL; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) m[t][r] = T(1.5) * id[t][r] - T(0.5) * y[t][r];
-    sign_prod<T, TB>(x, m, z);                                  // X <- X (3 I - X^2) / 2
-    if (odd || k == n2 - 1) {
-      sign_symmetrise<T, TB>(z, x, C);
-    } else {
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[t][r] = z[t][r];
-    }
-    odd ^= 1;
+    if (last) break;
   }
 }
 
@@ -2242,13 +2234,14 @@ __global__ __launch_bounds__(64) void k_admm_sign(ProjArgs a, const int32_t *__r
 // under a branch of its own), and the accumulators live only inside the
 // pass.  The loads of step s + 1 are issued before the steps of s; the
 // scheduling barrier keeps the compiler from hoisting all of them, which
-// would need more registers than a wave has.  With fred (only as L <- L M, no
-// transform), the wave also leaves its share of ||e I - L M||_F^2 (e I on the
-// first s vertices) in fred[wave], which every wave may read after the pass.
+// would need more registers than a wave has.  With fred, the wave also leaves
+// its share of ||L M||_F^2 - 2 wx ||x||_F^2 in fred[wave], which every wave may
+// read after the pass (for L = M = X and wx = 1 that is ||I - X^2||_F^2 less the
+// number of vertices: tr X^2 = ||X||_F^2; the sums need no masks).
 template <typename T, int N, int NTL>
 __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from_l, T alpha,
                                         T beta, T sa, T sb, int J, int g, int c, float *fred,
-                                        T e, int s) {
+                                        T wx) {
   constexpr int P = N + 1, STEPS = N / 4;
   typedef typename Mma<T>::v4 v4;
   const int jc = 16 * J + c;
@@ -2285,16 +2278,16 @@ __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from
     }
   }
   if (fred) {   // (uniform)
-    float q = 0.0f;
+    T off = T(0), dia = T(0), xx = T(0);
 #pragma unroll
-    for (int t = 0; t < NTL; ++t)
+    for (int r = 0; r < 4; ++r) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = 16 * (J + t) + sign16_row<T>(g, r);
-        const float d = (float)((i == jc && i < s ? e : T(0)) - acc[t][r]);
-        if (i >= jc) q += (i == jc ? 1.0f : 2.0f) * d * d;
-      }
-    q = wave_total_f32(q);
+      for (int t = 1; t < NTL; ++t) off += acc[t][r] * acc[t][r];
+      dia += acc[0][r] * acc[0][r];
+#pragma unroll
+      for (int K = 0; K < N / 16; ++K) xx += x[K][r] * x[K][r];
+    }
+    const float q = wave_total_f32((float)(dia + T(2) * (off - wx * xx)));
     if ((threadIdx.x & 63) == 0) fred[threadIdx.x >> 6] = q;
   }
   __syncthreads();   // every wave has read L
@@ -2332,8 +2325,18 @@ __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from
 // 1's clique step (X_k, Lambda_k and the five residual partials, as
 // k_admm_sign), 2 Algorithm 2's z-update (z_k and ||z_k - z_k_prev||^2), 3
 // Algorithm 3's cone step on the PSD blocks (as k_admm_sign's HSDE mode).
+// Waves per SIMD that k_sign_big's registers are held to: as many as its LDS
+// blocks let a compute unit take (two FP32 blocks of 128 of 8 waves: without
+// the bound 165 registers, one workgroup per unit and 1042 us for 1024 blocks
+// instead of 869; four FP64 blocks of 64: 348 -> 289 us), where the spills
+// that this costs stay at a few registers.
+template <typename T, int N>
+constexpr int sign_big_waves() {
+  return sizeof(T) == 4 ? (N <= 48 ? 6 : N <= 64 ? 5 : 4) : (N <= 48 ? 5 : N <= 64 ? 4 : N <= 96 ? 3 : 2);
+}
+
 template <typename T, int N, int MODE>
-__global__ __launch_bounds__(4 * N) void k_sign_big(ProjArgs a, const int32_t *__restrict__ list,
+__global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(ProjArgs a, const int32_t *__restrict__ list,
                                                     const int32_t *__restrict__ sizes,
                                                     const int64_t *__restrict__ offsets,
                                                     const T *__restrict__ in, T *__restrict__ out,
@@ -2475,16 +2478,16 @@ __global__ __launch_bounds__(4 * N) void k_sign_big(ProjArgs a, const int32_t *_
 
   const int ntu = __builtin_amdgcn_readfirstlane(nt);   // uniform per wave
   // one pass: L <- sa I + sb (L M), M from x or alpha I + beta L (from_l)
-  const auto pass = [&](bool from_l, T alpha, T beta, T sa, T sb, int gq, int cq, float *fr, T e) {
+  const auto pass = [&](bool from_l, T alpha, T beta, T sa, T sb, int gq, int cq, float *fr, T wx) {
     switch (ntu) {
-      case 8: if constexpr (TN >= 8) sb_pass<T, N, 8>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
-      case 7: if constexpr (TN >= 7) sb_pass<T, N, 7>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
-      case 6: if constexpr (TN >= 6) sb_pass<T, N, 6>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
-      case 5: if constexpr (TN >= 5) sb_pass<T, N, 5>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
-      case 4: if constexpr (TN >= 4) sb_pass<T, N, 4>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
-      case 3: sb_pass<T, N, 3>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
-      case 2: sb_pass<T, N, 2>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
-      default: sb_pass<T, N, 1>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, e, s); break;
+      case 8: if constexpr (TN >= 8) sb_pass<T, N, 8>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      case 7: if constexpr (TN >= 7) sb_pass<T, N, 7>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      case 6: if constexpr (TN >= 6) sb_pass<T, N, 6>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      case 5: if constexpr (TN >= 5) sb_pass<T, N, 5>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      case 4: if constexpr (TN >= 4) sb_pass<T, N, 4>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      case 3: sb_pass<T, N, 3>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      case 2: sb_pass<T, N, 2>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      default: sb_pass<T, N, 1>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
     }
   };
   // The passes of the fast steps (L = X X; L = 3 I + L (-3.2 I + 1.2 L);
@@ -2524,7 +2527,7 @@ __global__ __launch_bounds__(4 * N) void k_sign_big(ProjArgs a, const int32_t *_
           x[K][r] = L[(16 * K + sign16_row<T>(gq, r)) * P + 16 * J + cq];
     }
     if (ph == 0) {
-      float e2 = 0.0f;
+      float e2 = k == 0 ? 0.0f : (float)s;
 #pragma unroll
       for (int i = 0; i < NT / 64; ++i) e2 += fred[i];
       c1 = k == 0 ? (T)sign_scale(e2) : T(1);
