@@ -136,7 +136,8 @@ typedef struct {
                                    scalar elsewhere; 3 the matrix sign function, X_k = (W + W sign(W)) / 2 (no eigenvectors, no
                                    warm start), for cliques of up to 32 vertices (in one
                                    wave's registers) and in SDP_FP64 for all cliques (larger
-                                   ones with one block in LDS); the rest as with 0 */
+                                   ones with one block in LDS); the rest as with 0 (which
+                                   also takes it for SDP_FP32_EIG cliques of up to 48) */
   int32_t decouple;             /* 1 (SDP_FP32_EIG with warm_start = 1; blocks padded to 64
                                    and more; Algorithms 1-3 outside the unrolled iterations):
                                    a warm-started projection first separates the eigenspaces
@@ -146,12 +147,11 @@ typedef struct {
                                    the remaining opposite-sign mass is below the sweep
                                    tolerance and Gershgorin bounds certify both diagonal
                                    blocks, X is rebuilt from the positive block with no sweep;
-                                   otherwise the Jacobi sweeps continue from the refined basis
-                                   (and the clique skips the attempt for 4 iterations,
-                                   doubling after each further failure in a row, up to 64;
-                                   blocks of up to 96 with two or more failures in a row
-                                   use the matrix sign function instead of sweeps while
-                                   they wait).  The
+                                   otherwise the Jacobi sweeps continue from the refined
+                                   basis.  A clique whose attempts keep failing is projected
+                                   by the matrix sign function and tries again only in the
+                                   iterations 32, 64, 128, 256, 512 and every 512th after
+                                   that.  The
                                    result is P+(W) to the sweep tolerance either way.  With
                                    projection_method = 0 those blocks then take the scalar
                                    variants (which carry the decoupling).  Ignored for FP64
@@ -238,11 +238,11 @@ int sdp_projection_variants(int32_t dtype, int32_t cap, int32_t *block_n, int32_
  *              polynomial iterations on the matrix cores (k1 steps of
  *              X (3I - 3.2X^2 + 1.2X^4), then k2 of X (3I - X^2) / 2, as
  *              sdp_sign_schedule gives them).  It yields no eigenvectors: the
- *              standalone projections run it, and the solver's plans hold it
- *              only for the cliques of up to 32 vertices of Algorithms 1 and
- *              2 (projection_method 0 or 3; the one-wave variants of 16 and
- *              32), where the projection needs no eigenvectors; everything
- *              else in the solver is kind 0 or 1. */
+ *              standalone projections run it, and the solver's plans
+ *              (projection_method 0 or 3) for cliques of up to 32 vertices
+ *              (the one-wave variants of 16 and 32), in SDP_FP64 for all
+ *              cliques and with projection_method 0 in SDP_FP32_EIG for up to
+ *              48; everything else in the solver is kind 0 or 1. */
 int sdp_projection_variant_kind(int32_t dtype, int32_t variant, int32_t *kind);
 
 /* The steps of the sign iteration for blocks of n vertices and a tolerance
@@ -325,8 +325,8 @@ int sdp_diagnostics_noalloc(sdp_handle *h, sdp_result *res);
 int sdp_get_stats(sdp_handle *h, int64_t *jacobi_sweeps, int64_t *projections);
 
 /* The same statistics plus the number of projections since setup/reset that
- * took the matrix sign function as the fallback of a clique whose
- * decoupling certificate failed twice or more in a row (option decouple).
+ * took the matrix sign function in place of a clique's decoupling (option
+ * decouple).
  * Any pointer may be NULL. */
 int sdp_get_projection_stats(sdp_handle *h, int64_t *jacobi_sweeps, int64_t *projections,
                              int64_t *sign_fallbacks);

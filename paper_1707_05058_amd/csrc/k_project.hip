@@ -30,6 +30,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -42,6 +43,39 @@ namespace {
 // little room (||T||_F <= 3.4e-4).
 enum Mode { MODE_ADMM = 0, MODE_STANDALONE = 1, MODE_MINEIG = 2, MODE_ADMM_DEC = 3 };
 constexpr int DEC_MIN_N = 64;
+
+// When a clique takes the decoupling: one double per clique (its partial-sum
+// slot 7), 64 times the iterations since the record was cleared plus m.  m = 0:
+// the sign function projects it (k_sign_big, launched on the list before the
+// decoupling kernel), except in the probe iterations 32, 64, 128, ... 512 and
+// every 512th after that.  m = 1 + n: the last n attempts succeeded (n counts
+// to LONG).  An attempt that fails is finished by the Jacobi sweeps, which
+// leave a fresh basis; the clique tries again in the next iteration after a
+// probe or after LONG successes, else it goes back to the sign function.
+// Why: a decoupled projection of 40 FP32 cliques of 128 takes 130-210 us and
+// the sign function 150-270 us, sweeps 400-1050 us; in the early iterations, or
+// where both eigenvalue groups reach zero, the certificate fails, and sweeping
+// every time (or back-off waits that end at different times, so that some
+// clique sweeps in most iterations) cost 560-870 us per iteration on such
+// instances (now 220-430).  The probes are the same iterations for every
+// clique of an instance, so that their sweeps coincide.
+struct DecState {
+  static constexpr int LONG = 31;
+  int64_t it;
+  int n;   // -1: sign function
+  bool probe;
+  __device__ explicit DecState(double v) {
+    it = (int64_t)v >> 6;
+    n = (int)((int64_t)v & 63) - 1;
+    probe = it >= 32 && (it % 512 == 0 || (it < 512 && (it & (it - 1)) == 0));
+  }
+  __device__ bool sign() const { return n < 0 && !probe; }
+  __device__ double after_sign() const { return (double)((it + 1) * 64); }
+  __device__ double after_attempt(bool ok) const {
+    const int m = ok ? 1 + (n < LONG ? n + 1 : LONG) : n < 0 || n == LONG ? 1 : 0;
+    return (double)((it + 1) * 64 + m);
+  }
+};
 
 template <typename T> struct Num;
 template <> struct Num<float> {
@@ -551,100 +585,6 @@ __device__ bool decouple_blocks(T (&A)[(N / 2) * (N / 2) / NT][2][2],
   }
 }
 
-// P+(A) for a block held in registers (the scalar variants' 2 x 2 layout),
-// by the matrix sign function on the matrix cores: X0 = A / ||A||_F, k1
-// steps X <- X (3 I - 3.2 X^2 + 1.2 X^4), k2 steps X <- X (3 I - X^2) / 2,
-// then P+(A) = (A + A sign(A)) / 2, which replaces A in the registers.  The
-// products are the lower-tile ones (every iterate exactly symmetric); Abuf
-// and Vbuf are scratch.  For blocks whose eigenvalue groups both reach zero,
-// where the decoupling's certificate fails and the sweeps would need several
-// passes of N - 1 rounds.
-template <typename T, int N, int NT, int P>
-__device__ void sign_project_regs(T (&A)[(N / 2) * (N / 2) / NT][2][2], T *Abuf, T *Vbuf,
-                                  double *red, int k1, int k2) {
-  constexpr int K = N / 2;
-  constexpr int BPT = K * K / NT;
-  constexpr int AS = NT / K;
-  const auto ix = [](int r, int c) { return r * P + (c & 1) * K + (c >> 1); };
-  const auto slot = [](int q) { return q < K ? 2 * q : 2 * (q - K) + 1; };
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-  const int b = tid % K, a0 = tid / K;
-  double f2 = 0.0;
-#pragma unroll
-  for (int j = 0; j < BPT; ++j)
-#pragma unroll
-    for (int d = 0; d < 2; ++d)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) f2 += (double)A[j][d][e] * (double)A[j][d][e];
-  f2 = block_sum<NT>(f2, red);
-  const T scale = f2 > 0.0 ? (T)(1.0 / sqrt(f2)) : T(0);
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    const int aj = a0 + AS * j;
-#pragma unroll
-    for (int d = 0; d < 2; ++d)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) Abuf[ix(2 * aj + d, 2 * b + e)] = A[j][d][e] * scale;
-  }
-  __syncthreads();
-  const auto mirror_to = [&](T *buf) {
-    return [=](int qi, int qj, T v) {
-      if (qi >= qj) {
-        buf[slot(qi) * P + qj] = v;
-        buf[slot(qj) * P + qi] = v;
-      }
-    };
-  };
-  for (int it = 0; it < k1 + k2; ++it) {
-    // Y = X^2 into Vbuf
-    tile_product<T, N, NT, true>([&](int k, int q) { return Abuf[k * P + q]; },
-                                 [&](int k, int q) { return Abuf[k * P + q]; }, mirror_to(Vbuf));
-    __syncthreads();
-    if (it < k1) {
-      // Y (-3.2 I + 1.2 Y) over Y, then X (3 I + that) over X
-      tile_product<T, N, NT, true>(
-          [&](int k, int q) { return Vbuf[k * P + q]; },
-          [&](int k, int q) { return (k == slot(q) ? T(-3.2) : T(0)) + T(1.2) * Vbuf[k * P + q]; },
-          mirror_to(Vbuf));
-      __syncthreads();
-      tile_product<T, N, NT, true>(
-          [&](int k, int q) { return Abuf[k * P + q]; },
-          [&](int k, int q) { return (k == slot(q) ? T(3) : T(0)) + Vbuf[k * P + q]; },
-          mirror_to(Abuf));
-    } else {
-      tile_product<T, N, NT, true>(
-          [&](int k, int q) { return Abuf[k * P + q]; },
-          [&](int k, int q) { return (k == slot(q) ? T(1.5) : T(0)) - T(0.5) * Vbuf[k * P + q]; },
-          mirror_to(Abuf));
-    }
-    __syncthreads();
-  }
-  // A sign(A) with A into Vbuf, then P+(A) = (A + A sign(A)) / 2
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    const int aj = a0 + AS * j;
-#pragma unroll
-    for (int d = 0; d < 2; ++d)
-#pragma unroll
-      for (int e = 0; e < 2; ++e) Vbuf[ix(2 * aj + d, 2 * b + e)] = A[j][d][e];
-  }
-  __syncthreads();
-  tile_product<T, N, NT, true>([&](int k, int q) { return Vbuf[k * P + q]; },
-                               [&](int k, int q) { return Abuf[k * P + q]; }, mirror_to(Abuf));
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    const int aj = a0 + AS * j;
-#pragma unroll
-    for (int d = 0; d < 2; ++d)
-#pragma unroll
-      for (int e = 0; e < 2; ++e)
-        A[j][d][e] = T(0.5) * (A[j][d][e] + Abuf[ix(2 * aj + d, 2 * b + e)]);
-  }
-  __syncthreads();
-}
-
 template <typename T, int N, int NT, int MODE, bool BLK>
 __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__restrict__ list,
                                                 const int32_t *__restrict__ sizes,
@@ -742,9 +682,17 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
   const int a0 = tid / K;
   T A[BPT][2][2];
   T V[BPT][2][2];
-  // decoupling: iterations this clique still skips it (loaded early)
-  double dec_skip_left = 0.0;
-  if constexpr (DEC) dec_skip_left = a.part[NPART * (int64_t)cl + 7];
+  // decoupling: the clique's record
+  double dec_rec = 0.0;
+  if constexpr (DEC) {
+    dec_rec = a.part[NPART * (int64_t)cl + 7];
+    if (DecState(dec_rec).sign()) {   // k_sign_big has projected it (uniform)
+      __syncthreads();                // every thread has read the record
+      if (tid == 0 && !inst_done)
+        a.part[NPART * (int64_t)cl + 7] = DecState(dec_rec).after_sign();
+      return;
+    }
+  }
 
   // --- gather W_k = E_k U E_k^T - Lambda_k / rho (or the caller's block) ---
   double f2 = 0.0;
@@ -892,35 +840,12 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
   }
 
   // positive/negative decoupling instead of sweeps (warm-started ADMM blocks
-  // whose eigenvectors are not recorded).  After a failed attempt the clique
-  // skips it for a while, doubling the wait with every further failure in a
-  // row: dec_skip, 2 dec_skip, ... 16 dec_skip iterations (blocks whose two
-  // eigenvalue groups both reach zero fail the certificate every time); a
-  // success starts over.  Its partial-sum slot 7 keeps 256 level + wait.
-  bool dec = false, sgn = false;
+  // whose eigenvectors are not recorded)
+  bool dec = false;
   if constexpr (DEC) {
-    if (vw && !a.eig) {
-      double *flag = a.part + NPART * (int64_t)cl + 7;
-      const double v = dec_skip_left;
-      const int level = (int)(v * (1.0 / 256.0));
-      __syncthreads();   // every thread has read the counter before it changes
-      if (v - 256.0 * level > 0.0) {
-        if (tid == 0) *flag = v - 1.0;
-        // blocks of up to 96 with two or more failures in a row: the sign
-        // function instead of sweeps (for larger blocks its ~46 products
-        // cost more than the sweeps from the refined basis, which are few
-        // where failures are rare, as on the large workload's blocks of 128)
-        if (N <= 96 && level >= 2) {
-          sign_project_regs<T, N, NT, P>(A, Abuf, Vbuf, red, a.sign_k1, a.sign_k2);
-          sgn = true;
-        }
-      } else {
-        dec = decouple_blocks<T, N, NT, P>(A, V, Abuf, Vbuf, th, red, thr, a.dec_tmax2,
-                                           a.dec_max_ref);
-        const int nl = level < 5 ? level + 1 : 5;
-        if (tid == 0) *flag = dec ? 0.0 : 256.0 * nl + (double)(a.dec_skip << (nl - 1));
-      }
-    }
+    dec = decouple_blocks<T, N, NT, P>(A, V, Abuf, Vbuf, th, red, thr, a.dec_tmax2, a.dec_max_ref);
+    // (every thread read the clique's record before the gather's barriers)
+    if (tid == 0) a.part[NPART * (int64_t)cl + 7] = DecState(dec_rec).after_attempt(dec);
   }
 
   int sweep = 0;
@@ -949,7 +874,7 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
           if (WANT_V) V[j][d][e] = Vbuf[ix(2 * aj + d, 2 * b + e)];
     }
   }
-  for (; !BLK && !dec && !sgn && sweep < max_sweeps; ++sweep) {
+  for (; !BLK && !dec && sweep < max_sweeps; ++sweep) {
     double o2 = 0.0;
 #pragma unroll
     for (int j = 0; j < BPT; ++j) {
@@ -1148,8 +1073,7 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
     Abuf[slot(qi) * P + qj] = v;
     Abuf[slot(qj) * P + qi] = v;
   };
-  if (!BLK && (dec || sgn)) {
-    // (after the sign function M is P+(A) itself, a full matrix)
+  if (!BLK && dec) {
 #pragma unroll
     for (int j = 0; j < BPT; ++j) {
       const int aj = a0 + AS * j;
@@ -1158,11 +1082,11 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           const int r = 2 * aj + d, c = 2 * b + e;
-          Abuf[ix(r, c)] = (sgn || (th[r] > T(0) && th[c] > T(0))) ? A[j][d][e] : T(0);
+          Abuf[ix(r, c)] = (th[r] > T(0) && th[c] > T(0)) ? A[j][d][e] : T(0);
         }
     }
     __syncthreads();
-    if (COMPACT && !sgn) {
+    if (COMPACT) {
       const int kend = (npos + 3) & ~3;
       tile_product_part<T, N, NT, false>(
           npos, kend,
@@ -1313,7 +1237,7 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
       }
       pp[3] = p3;
       pp[5] = (double)sweep;
-      pp[6] = a.hsde ? p6 : (sgn ? 1.0 : 0.0);   // Algorithms 1, 2: sign fallback taken
+      pp[6] = a.hsde ? p6 : 0.0;   // Algorithms 1, 2: no sign fallback
     }
   }
 }
@@ -1632,7 +1556,10 @@ void sign_schedule(double tol, int n, int *k1_out, int *k2_out) {
 // Newton-Schulz steps that finish the iteration after one more fast step.
 // There every eigenvalue satisfies |1 - x_k^2| <= SIGN_THETA, so only the
 // starting points x_0 of the grid whose scalar iterates do are left, and the
-// bound 2 sqrt(n - 1) max e <= tol of sign_schedule is taken over those.
+// bound 2 sqrt(n - 1) max e <= tol of sign_schedule is taken over those, with
+// tol / 4: a quarter costs no step on most spectra (22.4 products instead of
+// 21.9 for FP32 blocks of 16) and keeps stopping early from using the budget
+// up.
 // (The first step scales X0 by c >= 1 with |c X0| <= SIGN_X_MAX: an eigenvalue
 // delta starts at x_0 = c delta, and |x_0| |1 - s| / 2 bounds its error.)
 SignPlan sign_plan(double tol, int n) {
@@ -1654,14 +1581,15 @@ SignPlan sign_plan(double tol, int n) {
   const auto newton = [](double v) { return v * (3.0 - v * v) / 2.0; };
   // Newton-Schulz steps after which the starting points marked in `in` meet
   // the bound from the iterates x (0 if not within `most`)
-  const auto steps = [&](std::vector<double> x, const std::vector<char> &in, int least, int most) {
+  const auto steps = [&](std::vector<double> x, const std::vector<char> &in, int least, int most,
+                         double bound) {
     for (int k2 = 1; k2 <= most; ++k2) {
       double e = 0.0;
       for (size_t j = 0; j < d.size(); ++j) {
         x[j] = newton(x[j]);
         if (in[j]) e = std::max(e, d[j] * std::fabs(1.0 - x[j]) / 2.0);
       }
-      if (k2 >= least && e <= target) return k2;
+      if (k2 >= least && e <= bound) return k2;
     }
     return 0;
   };
@@ -1671,12 +1599,13 @@ SignPlan sign_plan(double tol, int n) {
     for (size_t j = 0; j < d.size(); ++j) in[j] = std::fabs(1.0 - x[j] * x[j]) <= SIGN_THETA;
     for (double &v : x) v = fast(v);
     if (k == 0 || k >= SignPlan::KMAX) continue;
-    const int n2 = steps(x, in, 1, 15);
+    // (1.5e-16: what the double-precision iterates resolve)
+    const int n2 = steps(x, in, 1, 15, std::max(target / 4, std::min(target, 1.5e-16)));
     if (n2 > 0 && 3 * (k + 1) + 2 * n2 < 3 * pl.k1 + 2 * pl.k2) pl.set_steps_after(k, n2);
   }
   // the worst case from the scaled start (x_0 up to SIGN_X_MAX)
   std::fill(in.begin(), in.end(), 1);
-  const int n2 = steps(x, in, pl.k2, 12);
+  const int n2 = steps(x, in, pl.k2, 12, target);
   if (n2 > 0) pl.k2 = n2;
   cache.emplace(key, pl);
   return pl;
@@ -2222,51 +2151,69 @@ __global__ __launch_bounds__(64) void k_admm_sign(ProjArgs a, const int32_t *__r
   }
 }
 
-// One pass of k_sign_big for a wave with NTL lower tiles in column block J:
-// the product acc(t) = sum_k L(k, 16 (J + t) + c')^T M(k, J), M from x or
-// (from_l) alpha [k == j] + beta L(k, j); then, between barriers, the lower
+// Row pitch of k_sign_big's block.  FP32: N + 4, so that the four rows a wave
+// reads in a step (4 apart) sit on disjoint banks; FP64: odd (a pitch without
+// conflicts would cost a workgroup per unit at N = 64 and 96).
+template <typename T>
+__host__ __device__ constexpr int sign_big_pitch(int N) {
+  return sizeof(T) == 4 ? N + 4 : N + 1;
+}
+
+// One pass of k_sign_big for the wave of column block J (NTL = N / 16 - J lower
+// tiles): the product acc(t) = sum_k L(k, 16 (J + t) + c')^T M(k, J), M from x
+// or (FROM_L) alpha [k == j] + beta L(k, j); then, between barriers, the lower
 // tiles transformed to sa [i == j] + sb v into L on both sides of the
 // diagonal.  Step (K, r) of the product takes k = 16 K + R(g, r) from lane
 // group g (R the result-row map of the matrix cores: g + 4 r in FP64,
 // 4 g + r in FP32), which is where register r of tile K holds row k.  The
-// tile count is a template parameter, so each step's loads and matrix-core
-// steps form one straight block (a run-time bound puts every load and step
-// under a branch of its own), and the accumulators live only inside the
+// column block and the operand's source are template parameters, so each
+// step's loads and matrix-core steps form one straight block with constant
+// offsets (run-time bounds or sources put every load and step under a branch
+// of its own: with the source chosen at run time a pass over an FP32 block of
+// 128 took 7.3 us instead of 6.1), and the accumulators live only inside the
 // pass.  The loads of step s + 1 are issued before the steps of s; the
 // scheduling barrier keeps the compiler from hoisting all of them, which
 // would need more registers than a wave has.  With fred, the wave also leaves
 // its share of ||L M||_F^2 - 2 wx ||x||_F^2 in fred[wave], which every wave may
 // read after the pass (for L = M = X and wx = 1 that is ||I - X^2||_F^2 less the
 // number of vertices: tr X^2 = ||X||_F^2; the sums need no masks).
-template <typename T, int N, int NTL>
-__device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from_l, T alpha,
-                                        T beta, T sa, T sb, int J, int g, int c, float *fred,
-                                        T wx) {
-  constexpr int P = N + 1, STEPS = N / 4;
+template <typename T, int N, int NTL, bool FROM_L>
+__device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], T alpha, T beta, T sa,
+                                        T sb, int g, int c, float *fred, T wx) {
+  constexpr int P = sign_big_pitch<T>(N), STEPS = N / 4, J = N / 16 - NTL;
   typedef typename Mma<T>::v4 v4;
   const int jc = 16 * J + c;
-  const auto krow = [&](int K, int r) { return 16 * K + sign16_row<T>(g, r); };
+  const T *Lg = L + sign16_row<T>(g, 0) * P + c;   // row R(g, 0), column c
+  constexpr int RS = sizeof(T) == 4 ? 1 : 4;       // R(g, r) = R(g, 0) + RS r
+  const auto at = [&](int K, int r, int col16) { return Lg[(16 * K + RS * r) * P + 16 * col16]; };
   const auto bval = [&](int K, int r) {
-    const int k = krow(K, r);
-    return from_l ? (k == jc ? alpha : T(0)) + beta * L[k * P + jc] : x[K][r];
+    if constexpr (FROM_L) {
+      const T v = beta * at(K, r, J);
+      return (K == J && sign16_row<T>(g, r) == c) ? alpha + v : v;
+    } else {
+      return x[K][r];
+    }
   };
   v4 acc[NTL];
 #pragma unroll
   for (int t = 0; t < NTL; ++t) acc[t] = v4{0, 0, 0, 0};
   T av[NTL], b = bval(0, 0);
-  {
-    const int k = krow(0, 0);
 #pragma unroll
-    for (int t = 0; t < NTL; ++t) av[t] = L[k * P + jc + 16 * t];
-  }
+  for (int t = 0; t < NTL; ++t) av[t] = at(0, 0, J + t);
 #pragma unroll
   for (int st = 0; st < STEPS; ++st) {
     T an[NTL], bn = T(0);
     if (st + 1 < STEPS) {
-      const int K = (st + 1) >> 2, r = (st + 1) & 3, k = krow(K, r);
-      bn = bval(K, r);
+      const int K = (st + 1) >> 2, r = (st + 1) & 3;
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) an[t] = L[k * P + jc + 16 * t];
+      for (int t = 0; t < NTL; ++t) an[t] = at(K, r, J + t);
+      // (FROM_L: the column block's own diagonal tile, an[0])
+      if constexpr (FROM_L) {
+        const T v = beta * an[0];
+        bn = (K == J && sign16_row<T>(g, r) == c) ? alpha + v : v;
+      } else {
+        bn = x[K][r];
+      }
     }
 #pragma unroll
     for (int t = 0; t < NTL; ++t) acc[t] = Mma<T>::step(av[t], b, acc[t]);
@@ -2277,7 +2224,7 @@ __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from
       b = bn;
     }
   }
-  if (fred) {   // (uniform)
+  if (!FROM_L && fred) {   // (uniform)
     T off = T(0), dia = T(0), xx = T(0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -2296,8 +2243,8 @@ __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], bool from
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = 16 * (J + t) + sign16_row<T>(g, r);
-      if (i >= jc) {
-        const T v = (i == jc ? sa : T(0)) + sb * acc[t][r];
+      if (t > 0 || i >= jc) {
+        const T v = (t == 0 && i == jc ? sa : T(0)) + sb * acc[t][r];
         L[i * P + jc] = v;
         L[jc * P + i] = v;
       }
@@ -2341,7 +2288,7 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
                                                     const int64_t *__restrict__ offsets,
                                                     const T *__restrict__ in, T *__restrict__ out,
                                                     SignPlan pl) {
-  constexpr int P = N + 1, TN = N / 16, NT = 4 * N;
+  constexpr int P = sign_big_pitch<T>(N), TN = N / 16, NT = 4 * N;
   static_assert(N % 16 == 0 && N >= 48 && N <= 128, "column blocks of 16");
   __shared__ T L[N * P];
   __shared__ double red[6 * (NT / 64)];
@@ -2367,6 +2314,8 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
     inst_done = a.state[inst].done != 0;
     rho = a.state[inst].rho;
     if (MODE == 3) hf = a.hs[inst].f;
+    // beside the decoupling: only the cliques that do not take it (uniform)
+    if (a.sign_rest && !DecState(a.part[NPART * (int64_t)cl + 7]).sign()) return;
   }
   // packed position of (i, j) in the clique's lower triangle (i, j < s)
   const auto packed = [&](int i, int j) {
@@ -2478,17 +2427,21 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
 
   const int ntu = __builtin_amdgcn_readfirstlane(nt);   // uniform per wave
   // one pass: L <- sa I + sb (L M), M from x or alpha I + beta L (from_l)
-  const auto pass = [&](bool from_l, T alpha, T beta, T sa, T sb, int gq, int cq, float *fr, T wx) {
+  const auto pass = [&](auto from_l, T alpha, T beta, T sa, T sb, int gq, int cq, float *fr, T wx) {
+    constexpr bool FL = decltype(from_l)::value;
+#define SDP_SB_PASS(n) \
+  case n: if constexpr (TN >= n) sb_pass<T, N, n, FL>(L, x, alpha, beta, sa, sb, gq, cq, fr, wx); break;
     switch (ntu) {
-      case 8: if constexpr (TN >= 8) sb_pass<T, N, 8>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
-      case 7: if constexpr (TN >= 7) sb_pass<T, N, 7>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
-      case 6: if constexpr (TN >= 6) sb_pass<T, N, 6>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
-      case 5: if constexpr (TN >= 5) sb_pass<T, N, 5>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
-      case 4: if constexpr (TN >= 4) sb_pass<T, N, 4>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
-      case 3: sb_pass<T, N, 3>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
-      case 2: sb_pass<T, N, 2>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
-      default: sb_pass<T, N, 1>(L, x, from_l, alpha, beta, sa, sb, J, gq, cq, fr, wx); break;
+      SDP_SB_PASS(1)
+      SDP_SB_PASS(2)
+      SDP_SB_PASS(3)
+      SDP_SB_PASS(4)
+      SDP_SB_PASS(5)
+      SDP_SB_PASS(6)
+      SDP_SB_PASS(7)
+      SDP_SB_PASS(8)
     }
+#undef SDP_SB_PASS
   };
   // The passes of the fast steps (L = X X; L = 3 I + L (-3.2 I + 1.2 L);
   // L = L X, then x = L) and of the Newton-Schulz steps (L = 1.5 I -
@@ -2501,7 +2454,8 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
   // which spills.)
   // Bound: a workgroup per clique, by the matrix cores of its one compute
   // unit (67% of their FP64 peak for N = 128), so the number of passes counts.
-  int k = 0, n2 = pl.k2, ph = f2 == 0.0 ? 4 : pl.k1 > 0 ? 0 : 3;
+  int k = 0, n2 = pl.k2;
+  int ph = __builtin_amdgcn_readfirstlane(f2 == 0.0) ? 4 : pl.k1 > 0 ? 0 : 3;
   T c1 = T(1), c3 = T(1), c5 = T(1);
   bool last_fast = false;
   // ph: 0 Y, 1 Z, 2 X of a fast step; 3 Y, 5 X of a Newton-Schulz step; 4 S W
@@ -2516,8 +2470,11 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
       sa = T(1.5);
       sb = T(-0.5);
     }
-    pass(ph == 1, T(-3.2) * c3, T(1.2) * c5, sa, sb, gq, cq, ph == 0 ? fred : nullptr,
-         k == 0 ? T(0) : T(1));
+    if (ph == 1)
+      pass(std::true_type(), T(-3.2) * c3, T(1.2) * c5, sa, sb, gq, cq, nullptr, T(0));
+    else
+      pass(std::false_type(), T(0), T(0), sa, sb, gq, cq, ph == 0 ? fred : nullptr,
+           k == 0 ? T(0) : T(1));
     if (ph == 4) break;
     if (ph == 2 || ph == 5) {
 #pragma unroll
@@ -2533,11 +2490,16 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
       c1 = k == 0 ? (T)sign_scale(e2) : T(1);
       c3 = c1 * c1 * c1;
       c5 = c3 * c1 * c1;
-      const int stop = pl.steps_after(k);
-      last_fast = k > 0 && stop > 0 && e2 <= SIGN_THETA * SIGN_THETA;
-      if (last_fast) n2 = stop;
+      // (the same in every lane; the broadcast tells the compiler, which
+      // otherwise masks lanes off through the passes)
+      const int near1 = __builtin_amdgcn_readfirstlane(e2 <= SIGN_THETA * SIGN_THETA);
+      const int stop = pl.steps_after(k);   // (0 for k = 0)
       ++k;
-      last_fast = __builtin_amdgcn_readfirstlane(last_fast || k == pl.k1);
+      last_fast = k == pl.k1;
+      if (near1 && stop > 0) {
+        last_fast = true;
+        n2 = stop;
+      }
       ph = 1;
     } else if (ph == 1) {
       ph = 2;
@@ -2619,7 +2581,8 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
     }
     pp[3] = pv[3];
     pp[5] = 0.0;     // no Jacobi sweeps
-    pp[6] = pv[5];   // Algorithm 3: ||u_t||^2; else 0 (no sign fallback)
+    // Algorithm 3: ||u_t||^2; else whether this was the decoupling's fallback
+    pp[6] = MODE == 3 ? pv[5] : a.sign_rest ? 1.0 : 0.0;
   }
 }
 
@@ -3042,14 +3005,44 @@ int64_t split_workspace(int precision, int variant, int count) {
   return (int64_t)count * (4 * N * N + SPLIT_META);
 }
 
+// k_sign_big on a list of cliques, in the mode of the algorithm.
+template <typename T>
+hipError_t launch_sign_big(int N, const int32_t *list, int count, const ProjArgs &a,
+                           const SignPlan &pl, hipStream_t st) {
+  if (count <= 0) return hipSuccess;
+#define SDP_ADMM_BIG(n)                                                                        \
+  if (N == n) {                                                                                \
+    if (a.hsde)                                                                                \
+      hipLaunchKernelGGL((k_sign_big<T, n, 3>), dim3(count), dim3(4 * n), 0, st, a, list,      \
+                         nullptr, nullptr, nullptr, nullptr, pl);                              \
+    else if (a.dual)                                                                           \
+      hipLaunchKernelGGL((k_sign_big<T, n, 2>), dim3(count), dim3(4 * n), 0, st, a, list,      \
+                         nullptr, nullptr, nullptr, nullptr, pl);                              \
+    else                                                                                       \
+      hipLaunchKernelGGL((k_sign_big<T, n, 1>), dim3(count), dim3(4 * n), 0, st, a, list,      \
+                         nullptr, nullptr, nullptr, nullptr, pl);                              \
+    return hipGetLastError();                                                                  \
+  }
+  SDP_ADMM_BIG(48)
+  SDP_ADMM_BIG(64)
+  SDP_ADMM_BIG(80)
+  SDP_ADMM_BIG(96)
+  if constexpr (sizeof(T) == 4) {
+    SDP_ADMM_BIG(112)
+  }
+  SDP_ADMM_BIG(128)
+#undef SDP_ADMM_BIG
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_admm_projection(int precision, int variant, const int32_t *list, int count,
                                   const ProjArgs &a, hipStream_t st, double *split_ws) {
   int N, NT;
   projection_variant_info(precision, variant, &N, &NT);
   if (projection_variant_kind(precision, variant) == 2) {
     // sign-function lists (Algorithms 1, 2 and 3): the register kernels for
-    // blocks of 16 and 32, below the one-block LDS kernel for FP64 blocks of
-    // 48-128; a caller that needs eigenvectors (the unrolled forward records
+    // blocks of 16 and 32, below the one-block LDS kernel for blocks of 48
+    // and more; a caller that needs eigenvectors (the unrolled forward records
     // V, theta) gets the Jacobi default of the same block size
     if (!a.eig && NT == 64 && (N == 16 || N == 32)) {
       if (count <= 0) return hipSuccess;
@@ -3078,10 +3071,10 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
 #undef SDP_ADMM_SIGN
       return hipGetLastError();
     }
-    // FP64 cliques of 33-128: one block in LDS, the other operand in
-    // registers (cliques of 97-128 have no variant with eigenvectors: the
-    // plan refuses the unrolled iterations for them)
-    if (precision == 0 && N >= 48 && NT == 4 * N && !a.eig) {
+    // larger cliques: one block in LDS, the other operand in registers (FP64
+    // cliques of 97-128 have no variant with eigenvectors: the plan refuses
+    // the unrolled iterations for them)
+    if (N >= 48 && NT == 4 * N && !a.eig) {
       if (count <= 0) return hipSuccess;
       const SignPlan pl = sign_plan(a.tol, N);
       if (split_ws && split_workspace(precision, variant, count) > 0) {
@@ -3097,26 +3090,8 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
 #undef SDP_SPLIT
         return hipErrorInvalidValue;
       }
-#define SDP_ADMM_BIG(n)                                                                        \
-  if (N == n) {                                                                                \
-    if (a.hsde)                                                                                \
-      hipLaunchKernelGGL((k_sign_big<double, n, 3>), dim3(count), dim3(4 * n), 0, st, a, list,  \
-                         nullptr, nullptr, nullptr, nullptr, pl);                              \
-    else if (a.dual)                                                                           \
-      hipLaunchKernelGGL((k_sign_big<double, n, 2>), dim3(count), dim3(4 * n), 0, st, a, list,  \
-                         nullptr, nullptr, nullptr, nullptr, pl);                              \
-    else                                                                                       \
-      hipLaunchKernelGGL((k_sign_big<double, n, 1>), dim3(count), dim3(4 * n), 0, st, a, list,  \
-                         nullptr, nullptr, nullptr, nullptr, pl);                              \
-    return hipGetLastError();                                                                  \
-  }
-      SDP_ADMM_BIG(48)
-      SDP_ADMM_BIG(64)
-      SDP_ADMM_BIG(80)
-      SDP_ADMM_BIG(96)
-      SDP_ADMM_BIG(128)
-#undef SDP_ADMM_BIG
-      return hipErrorInvalidValue;
+      return precision == 1 ? launch_sign_big<float>(N, list, count, a, pl, st)
+                            : launch_sign_big<double>(N, list, count, a, pl, st);
     }
     if (precision == 0 && N == 128) return hipErrorInvalidValue;   // needs eigenvectors
     variant = projection_default_variant(precision, N);
@@ -3124,6 +3099,12 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
   }
   const int blk = projection_variant_two_level(precision, variant);
   if (a.decouple && a.vw && !a.eig) {
+    if (precision == 1 && !blk && N >= DEC_MIN_N) {
+      ProjArgs w = a;   // the cliques that do not take the decoupling now
+      w.sign_rest = 1;
+      const hipError_t e = launch_sign_big<float>(N, list, count, w, sign_plan(a.tol, N), st);
+      if (e != hipSuccess) return e;
+    }
     if (precision == 1)
       return dispatch<float, MODE_ADMM_DEC>(N, NT, blk, count, a, list, nullptr, nullptr, nullptr,
                                             nullptr, nullptr, a.max_sweeps, a.tol, st);

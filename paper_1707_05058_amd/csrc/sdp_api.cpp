@@ -109,14 +109,18 @@ int default_variant(int precision, int s, int method) {
 
 // The sign-function variant the solver's plan takes for cliques of s
 // vertices: the register-resident kernels (one wave, N = 16 or 32) for
-// s <= 32; in FP64 also the one-block LDS kernel (NT = 4N) of the smallest
-// fitting N for 33-128 (measured against the warm-started Jacobi kernels:
-// nonchordal workload FP64 1046 -> 1439 iter/s, batched 72.3 -> 75.8; in
-// FP32 the Jacobi kernels and the decoupling stay faster, batched 93.4 ->
-// 92.2 with the sign function for blocks of 48).  -1 otherwise.
-int sign_variant(int precision, int s) {
-  const bool big = precision == 0 && s > 32;
-  if (s > 32 && !big) return -1;
+// s <= 32; above, the one-block LDS kernel (NT = 4N) of the smallest fitting
+// N, in FP64 for all, in FP32 for up to max_fp32 vertices.  -1 otherwise.
+// SIGN_FP32_MAX: warm-started Jacobi of 40 / 300 FP32 cliques of 40 vertices
+// takes 63 us and a settled iteration 82 / 149 us, the sign function 36-42 and
+// 56 / 126 us; from 49 vertices on a settled iteration is cheaper decoupled
+// (300 cliques of 56: 162 us against 177), and the sign function takes the
+// iterations in which the decoupling fails.
+constexpr int SIGN_FP32_MAX = 48;
+
+int sign_variant(int precision, int s, int max_fp32) {
+  const bool big = s > 32;
+  if (big && precision == 1 && s > max_fp32) return -1;
   const int n = s + (s & 1);
   int best = -1, bestN = 1 << 30;
   for (int v = 0; v < projection_variant_count(precision); ++v) {
@@ -809,7 +813,9 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
                              ? 1
                              : pm;
       for (auto &kv : count_of_size) {
-        int sv = sign_lists ? sign_variant(h->precision, kv.first) : -1;
+        int sv = sign_lists ? sign_variant(h->precision, kv.first,
+                                           opt.projection_method == 0 ? SIGN_FP32_MAX : 32)
+                            : -1;
         if (fitting_variants(h->precision, kv.first, 0).empty()) {
           // FP64 cliques of 97-128: the sign-function kernel is the only one
           sv = big_sign_variant(h->precision, kv.first);
@@ -1033,10 +1039,6 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     p.tol = h->jac_tol;
     p.decouple = opt.decouple && h->precision == SDP_FP32_EIG;
     p.dec_max_ref = h->precision == SDP_FP32_EIG ? 2 : 3;
-    p.dec_skip = 4;
-    // the sign-function fallback of cliques (of up to 96 vertices) whose
-    // certificate keeps failing: P+ to the sweep tolerance
-    sign_schedule(h->jac_tol, 96, &p.sign_k1, &p.sign_k2);
     // the rotation Q = I + T + T^2 / 2 has Q^T Q - I = T^4 / 4, at most
     // ||T||_F^4 / 4: with ||T||_F^2 <= sqrt(tol / 0.75) that stays below a
     // third of the sweep tolerance (the bound limits the refinements to

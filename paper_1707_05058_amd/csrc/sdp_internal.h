@@ -95,10 +95,9 @@ struct ProjArgs {
   int max_sweeps;
   double tol;
   // positive/negative decoupling of warm-started blocks: on/off, refinements
-  // per attempt, iterations a clique skips it after a failed attempt, bound
-  // on ||T||_F^2 for one Newton-Schulz step
-  int decouple, dec_max_ref, dec_skip;
-  int sign_k1, sign_k2;   // sign-function steps for cliques whose decoupling keeps failing
+  // per attempt, bound on ||T||_F^2 for one Newton-Schulz step
+  int decouple, dec_max_ref;
+  int sign_rest;          // k_sign_big: only the cliques that do not take the decoupling now
   double dec_tmax2;
   void *eig;              // optional: per clique V (s x N) then theta (N), precision T
   const int64_t *eig_off; // element offset of each clique's record in eig
