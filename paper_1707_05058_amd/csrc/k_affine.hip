@@ -21,6 +21,10 @@
 
 #include <math.h>
 
+#include <algorithm>
+#include <type_traits>
+#include <vector>
+
 namespace {
 
 constexpr int ROW_NT = 256;   // threads of a row-dot workgroup
@@ -234,6 +238,245 @@ __global__ __launch_bounds__(COL_NT) void k_coldot(AffineArgs a) {
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Both products with B in one pass over it (dense instances of Algorithms 1
+// and 2):  y1 = B v - L^-1 b  and the partial sums of  B^T y1.
+// A row of B takes part in the second product as soon as its own entry of y1
+// is known, so B is read once if the row stays on the chip until then.  A row
+// is too long for one compute unit's registers beside its share of the sums,
+// so a cluster of G workgroups (one per unit, FU_COLS columns each) shares a
+// group of rows: every member keeps its columns of FU_R rows in registers,
+// forms its part of their dot products, exchanges the parts with the other
+// members, adds y1_i times the rows to its column sums and loads the next
+// rows.  (A unit waits 2-3 us for an exchange with no load in flight, but the
+// clusters are not in step, and the others' loads fill the memory pipes: a
+// unit's 256 KB take 9.6 us at its share of the bandwidth and 2 us alone.)
+// The column sums of a row group go to memory once; k_fused_reduce adds the
+// groups in order.
+// Exchange: one slot per (row, member), two 64-bit words that each carry half
+// of the value and the launch's tag, written and read as relaxed atomics: a
+// word with the right tag is the value, so no fence is needed (a release fence
+// writes back the XCD's L2).  The tag is a counter on the device that
+// k_fused_reduce advances.  Nothing relies on the members running at the same
+// time: a member that has polled FU_SPIN times computes the missing parts
+// itself, with the same arithmetic, so the results do not depend on it.
+// Bound: HBM; 8 (rows + 2 groups) bytes per column instead of 16 rows.
+// FUSED_FIGURES
+// ---------------------------------------------------------------------------
+constexpr int FU_NT = 512;                 // threads: one workgroup per unit
+constexpr int FU_K = 4;                    // pairs of columns per thread
+constexpr int FU_R = 8;                    // rows at a time
+constexpr int FU_COLS = 2 * FU_NT * FU_K;  // most columns of a member
+constexpr int FU_MAXG = 16;                // most members of a cluster
+constexpr int FU_SPIN = 400;
+constexpr int64_t FUSED_MIN_BYTES = 1 << 20;
+
+// Sum over each row of 16 lanes, the same in every lane of the row.
+__device__ inline double row16_sum(double v) {
+  const auto ror = [](double x, auto ctrl) {
+    constexpr int C = decltype(ctrl)::value;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), C, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), C, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+  };
+  v += ror(v, std::integral_constant<int, 0x128>());   // row_ror:8
+  v += ror(v, std::integral_constant<int, 0x124>());   // row_ror:4
+  v += ror(v, std::integral_constant<int, 0x122>());   // row_ror:2
+  v += ror(v, std::integral_constant<int, 0x121>());   // row_ror:1
+  return v;
+}
+
+// The pair `off` bytes past a row pointer that is the same in every lane (an
+// unsigned 32-bit offset: the address needs no vector registers of its own).
+template <bool NTL>
+__device__ inline dvec2 load_pair(const double *row, uint32_t off) {
+  const dvec2 *p = reinterpret_cast<const dvec2 *>(reinterpret_cast<const char *>(row) + off);
+  if constexpr (NTL) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
+template <bool NTL>
+__global__ __launch_bounds__(FU_NT, 2) void k_fused(AffineArgs a) {
+  const FusedTile ft = a.fu_tiles[blockIdx.x];
+  const InstDesc d = a.inst[ft.inst];
+  if (!a.ignore_done && a.state[ft.inst].done) return;
+  const uint32_t tag = *a.fu_tag;
+  const double bs = a.dual ? -1.0 / a.state[ft.inst].rho : 1.0;
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int col0 = ft.member * ft.chunk, ncol = min(ft.chunk, d.ld - col0);
+  const double *mat = a.Bm + d.a_off;
+  const double *vec = a.v + d.coord_off;
+  // rows past the group's end repeat its last row (and are left out below)
+  const auto row_ptr = [&](int row) { return mat + (int64_t)min(row, ft.row1 - 1) * d.ld; };
+  // pairs of columns past the member's end read its first pair, against v = 0
+  uint32_t off[FU_K];   // bytes
+  double2 v[FU_K], acc[FU_K];
+#pragma unroll
+  for (int k = 0; k < FU_K; ++k) {
+    const int c = 2 * (tid + FU_NT * k), o = col0 + (c < ncol ? c : 0);
+    off[k] = 8u * (uint32_t)o;
+    v[k] = *reinterpret_cast<const double2 *>(vec + o);
+    if (c >= ncol) v[k] = make_double2(0.0, 0.0);
+    acc[k] = make_double2(0.0, 0.0);
+  }
+  __shared__ double red[FU_R][16];        // [row][wave] (waves 8..15: zero)
+  __shared__ double ysh[FU_R];
+  __shared__ double peer[FU_R][FU_MAXG];  // parts computed in place of a member
+  __shared__ int late;
+  if (tid < FU_R * 16) (&red[0][0])[tid] = 0.0;
+  if (tid == 0) late = 0;
+  __syncthreads();
+  // the first two waves' (row, member): row sr, lane groups of 16
+  const int sr = 4 * (w & 1) + (l >> 4), sm = l & 15;
+  const bool head = w < FU_R / 4;
+  // a row's share of a thread, in a fixed order of fused operations
+  const auto fma_pair = [](const dvec2 &m, const double2 &x, double t) {
+    return __builtin_fma(m.y, x.y, __builtin_fma(m.x, x.x, t));
+  };
+  const auto wave_part = [&](double t, int r) {   // the wave's sum of t, for row r
+    t = row16_sum(t);
+    t += __shfl_xor(t, 16, 64);
+    t += __shfl_xor(t, 32, 64);
+    if (l == 0) red[r][w] = t;
+  };
+  // afterwards every lane of the head waves holds the workgroup's part of row sr
+  const auto wg_part = [&]() {
+    __syncthreads();
+    return head ? row16_sum(red[sr][sm]) : 0.0;
+  };
+  // y1 of the rows from the members' parts s (lane sm: member sm's)
+  const auto finish = [&](double s, int row) {
+    const int64_t g = d.row_off + row;
+    double y = row16_sum(s);
+    y = row < ft.row1 ? y - bs * a.bp[g] : 0.0;
+    if (sm == 0) {
+      ysh[sr] = y;
+      if (ft.member == 0 && row < ft.row1) a.y1[g] = y;
+    }
+  };
+  dvec2 m[FU_R][FU_K];
+  for (int row0 = ft.row0; row0 < ft.row1; row0 += FU_R) {
+#pragma unroll
+    for (int r = 0; r < FU_R; ++r) {
+      const double *p = row_ptr(row0 + r);
+#pragma unroll
+      for (int k = 0; k < FU_K; ++k) m[r][k] = load_pair<NTL>(p, off[k]);
+    }
+#pragma unroll
+    for (int r = 0; r < FU_R; ++r) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < FU_K; ++k) t = fma_pair(m[r][k], v[k], t);
+      wave_part(t, r);
+    }
+    const double own = wg_part();
+    if (head) {
+      const int row = row0 + sr;
+      const bool live = row < ft.row1 && sm < ft.size;
+      double s = sm == ft.member ? own : 0.0;
+      bool ready = !live || sm == ft.member;
+      unsigned long long *q = a.fu_slots + 2 * ((d.row_off + row) * FU_MAXG + sm);
+      if (live && sm == ft.member && ft.size > 1) {
+        const unsigned long long t = (unsigned long long)tag << 32;
+        __hip_atomic_store(q, t | (unsigned)__double2loint(own), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(q + 1, t | (unsigned)__double2hiint(own), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      }
+      for (int n = 0; n < FU_SPIN && __ballot(!ready) != 0; ++n) {
+        if (!ready) {
+          const unsigned long long lo =
+              __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const unsigned long long hi =
+              __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if ((uint32_t)(lo >> 32) == tag && (uint32_t)(hi >> 32) == tag) {
+            s = __hiloint2double((int)(uint32_t)hi, (int)(uint32_t)lo);
+            ready = true;
+          }
+        }
+      }
+      if (__ballot(!ready) != 0 && l == 0) late = 1;
+      finish(s, row);
+    }
+    __syncthreads();
+    // (the same in every wave; the broadcast tells the compiler)
+    if (__builtin_amdgcn_readfirstlane(late)) {   // compute the other members' parts
+      __syncthreads();                            // every wave has read the flag
+      if (tid == 0) late = 0;
+      for (int mb = 0; mb < ft.size; ++mb) {
+        const int c0 = mb * ft.chunk, nc = min(ft.chunk, d.ld - c0);
+#pragma unroll 1
+        for (int r = 0; r < FU_R; ++r) {
+          double t = 0.0;
+#pragma unroll 1
+          for (int k = 0; k < FU_K; ++k) {
+            const int c = 2 * (tid + FU_NT * k), o = c0 + (c < nc ? c : 0);
+            double2 x = *reinterpret_cast<const double2 *>(vec + o);
+            if (c >= nc) x = make_double2(0.0, 0.0);
+            t = fma_pair(load_pair<NTL>(row_ptr(row0 + r), 8u * (uint32_t)o), x, t);
+          }
+          wave_part(t, r);
+        }
+        const double pv = wg_part();
+        if (head && sm == 0) peer[sr][mb] = pv;
+        __syncthreads();
+      }
+      if (head) finish(sm < ft.size ? peer[sr][sm] : 0.0, row0 + sr);
+      __syncthreads();
+    }
+    // the rows into the column sums
+#pragma unroll
+    for (int r = 0; r < FU_R; ++r) {
+      const double y = ysh[r];
+#pragma unroll
+      for (int k = 0; k < FU_K; ++k) {
+        acc[k].x += y * m[r][k].x;
+        acc[k].y += y * m[r][k].y;
+      }
+    }
+  }
+  double *out = a.fu_part + ft.part_off + col0;
+#pragma unroll
+  for (int k = 0; k < FU_K; ++k) {
+    const int c = 2 * (tid + FU_NT * k);
+    if (c < ncol) *reinterpret_cast<double2 *>(out + c) = acc[k];
+  }
+}
+
+// u = (bhat - sum over row groups of the column sums) / D; one workgroup per
+// 128 columns of an instance, its waves dealt the groups.
+__global__ __launch_bounds__(256) void k_fused_reduce(AffineArgs a) {
+  const int inst = a.col_tiles[2 * blockIdx.x], col0 = a.col_tiles[2 * blockIdx.x + 1];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.fu_tag += 1;   // the next launch's tag
+  const InstDesc d = a.inst[inst];
+  if (!a.ignore_done && a.state[inst].done) return;
+  const int64_t p0 = a.fu_part_first[2 * inst];
+  const int groups = (int)a.fu_part_first[2 * inst + 1];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, col = col0 + 2 * l;
+  double2 s = make_double2(0.0, 0.0);
+  if (col < d.ld) {
+    const double *p = a.fu_part + p0 + col;
+#pragma unroll 8
+    for (int g = w; g < groups; g += 4) {
+      const double2 q = *reinterpret_cast<const double2 *>(p + (int64_t)g * d.ld);
+      s.x += q.x;
+      s.y += q.y;
+    }
+  }
+  __shared__ double2 red[4][64];
+  red[w][l] = s;
+  __syncthreads();
+  if (w != 0 || col >= d.ld) return;
+#pragma unroll
+  for (int i = 1; i < 4; ++i) {
+    s.x += red[i][l].x;
+    s.y += red[i][l].y;
+  }
+  const int64_t g = d.coord_off + col;
+  a.u[g] = (a.bhat[g] - s.x) / a.D[g];
+  a.u[g + 1] = (a.bhat[g + 1] - s.y) / a.D[g + 1];
 }
 
 // ---------------------------------------------------------------------------
@@ -683,7 +926,12 @@ hipError_t launch_affine_stage(const AffineArgs &a, int stage, hipStream_t st) {
       break;
     }
     case 1:
-      launch_dense_rowdot(a, st);
+      if (a.fu_ntiles > 0 && a.Bm) {
+        if (a.stream_nt) hipLaunchKernelGGL(k_fused<true>, dim3(a.fu_ntiles), dim3(FU_NT), 0, st, a);
+        else hipLaunchKernelGGL(k_fused<false>, dim3(a.fu_ntiles), dim3(FU_NT), 0, st, a);
+      } else {
+        launch_dense_rowdot(a, st);
+      }
       if (a.n_csr_rows > 0)
         hipLaunchKernelGGL(k_csr_rowdot, dim3((a.n_csr_rows + 3) / 4), dim3(256), 0, st, a);
       break;
@@ -696,7 +944,10 @@ hipError_t launch_affine_stage(const AffineArgs &a, int stage, hipStream_t st) {
         hipLaunchKernelGGL(k_trmv_wave<1>, dim3((a.n_t3_rows + 3) / 4), dim3(256), 0, st, a);
       break;
     case 4:
-      launch_dense_coldot<0>(a, st);
+      if (a.fu_ntiles > 0 && a.Bm)
+        hipLaunchKernelGGL(k_fused_reduce, dim3(a.n_col_tiles), dim3(256), 0, st, a);
+      else
+        launch_dense_coldot<0>(a, st);
       if (a.n_csc_cols > 0)
         hipLaunchKernelGGL(k_csc_coldot<0>, dim3(a.n_csc_cols), dim3(256), 0, st, a);
       break;
@@ -723,6 +974,54 @@ hipError_t launch_objective(const AffineArgs &a, double *obj, hipStream_t st) {
   hipLaunchKernelGGL(k_objective, dim3(a.batch), dim3(256), 0, st, a, obj);
   return hipGetLastError();
 }
+
+// The fused pass's tiles for the dense instances (m, ld) of a handle: empty
+// where it would not pay.  A cluster of G = ceil(ld / FU_COLS) workgroups
+// takes a group of rows; one workgroup runs per compute unit, so the groups
+// are as long as fills the chip once (256 workgroups), up to FU_GROUP rows,
+// past which the column sums (written and read once per group) are below 2%
+// of B.
+FusedPlan plan_fused(const std::vector<InstDesc> &inst) {
+  constexpr int UNITS = 256, FU_GROUP = 128;
+  FusedPlan p;
+  int64_t chunks = 0, bytes = 0;
+  for (const InstDesc &d : inst) {
+    if (d.a_format != 0 || d.m <= 0) continue;
+    const int G = (d.ld + FU_COLS - 1) / FU_COLS;
+    if (G > FU_MAXG) return FusedPlan();
+    chunks += (int64_t)d.m * G;
+    bytes += 8 * (int64_t)d.m * d.ld;
+  }
+  if (bytes < FUSED_MIN_BYTES) return FusedPlan();
+  const auto count = [&](int64_t rows) {
+    int64_t n = 0;
+    for (const InstDesc &d : inst)
+      if (d.a_format == 0) n += (d.m + rows - 1) / rows * ((d.ld + FU_COLS - 1) / FU_COLS);
+    return n;
+  };
+  int64_t rows = std::max<int64_t>((chunks + UNITS - 1) / UNITS, 1);
+  while (rows <= FU_GROUP && count(rows) > UNITS) ++rows;
+  rows = std::min<int64_t>(rows, FU_GROUP);
+  p.part_first.assign(2 * inst.size(), 0);
+  for (size_t i = 0; i < inst.size(); ++i) {
+    const InstDesc &d = inst[i];
+    if (d.a_format != 0 || d.m <= 0) continue;
+    const int G = (d.ld + FU_COLS - 1) / FU_COLS;
+    const int chunk = ((d.ld + G - 1) / G + 63) / 64 * 64;
+    const int groups = (int)((d.m + rows - 1) / rows);
+    p.part_first[2 * i] = p.part_doubles;
+    p.part_first[2 * i + 1] = groups;
+    for (int g = 0; g < groups; ++g) {
+      // rows split evenly over the groups
+      const int r0 = (int)((int64_t)d.m * g / groups), r1 = (int)((int64_t)d.m * (g + 1) / groups);
+      for (int mb = 0; mb < G; ++mb)
+        p.tiles.push_back(FusedTile{(int32_t)i, r0, r1, mb, G, chunk, p.part_doubles});
+      p.part_doubles += d.ld;
+    }
+  }
+  return p;
+}
+int64_t fused_slots_per_row() { return 2 * FU_MAXG; }
 
 int affine_col_tile_width() { return COL_W; }
 int affine_cg_tile_rows() { return CG_ROWS; }

@@ -1014,6 +1014,15 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     } else if (d_A && !cg) {
       a.Bm = dev_zeros<double>(aoff, own);
       a.bp = dev_zeros<double>(row, own);
+      const FusedPlan fp = plan_fused(h->desc);
+      if (!fp.tiles.empty()) {
+        a.fu_tiles = dev_upload(fp.tiles, own);
+        a.fu_ntiles = (int)fp.tiles.size();
+        a.fu_slots = dev_zeros<unsigned long long>(fused_slots_per_row() * row, own);
+        a.fu_tag = dev_upload(std::vector<uint32_t>(1, 1u), own);   // (cleared slots: tag 0)
+        a.fu_part = dev_zeros<double>(fp.part_doubles, own);
+        a.fu_part_first = dev_upload(fp.part_first, own);
+      }
     }
     a.csr_rows = dev_upload(csr_rows, own);
     a.n_csr_rows = (int)(csr_rows.size() / 2);

@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #define SDP_WAVE 64
 // per-clique partial sums: ||X_k - H_k x||^2, ||X_k||^2, ||H_k x||^2,
 // ||X_k - X_k^prev||^2, ||Lambda_k||^2 (full Frobenius), Jacobi sweeps
@@ -191,6 +193,14 @@ int projection_max_size(int precision);
 // ----------------------------------------------------------------------------
 // Affine step and reductions (k_affine.hip)
 // ----------------------------------------------------------------------------
+// One workgroup of the fused pass over B: columns member * chunk .. of rows
+// row0 .. row1 - 1, in a cluster of `size` members; its column sums go to
+// part_off (+ its first column) of the partial sums.
+struct FusedTile {
+  int32_t inst, row0, row1, member, size, chunk;
+  int64_t part_off;
+};
+
 struct AffineArgs {
   const InstDesc *inst;
   InstState *state;
@@ -241,6 +251,12 @@ struct AffineArgs {
   const int32_t *cg_tiles; int cg_ntiles;     // (inst, first row) per tile of rows
   const int32_t *cg_tile_first;               // [batch + 1]: an instance's tiles
   double *cg_part;                            // [3][cg_ntiles]: p^T M p, r^T z, ||r||^2
+  // both products with B in one pass (fu_ntiles > 0, with Bm)
+  const FusedTile *fu_tiles; int fu_ntiles;
+  unsigned long long *fu_slots;               // exchange: fused_slots_per_row() words per row
+  uint32_t *fu_tag;                           // tag of the next launch
+  double *fu_part;                            // column sums: ld per row group
+  const int64_t *fu_part_first;               // per instance: offset of its first group, groups
   int cg_loop;                                // products inside the solve: skip stopped instances
   int stream_nt;                              // dense passes with non-temporal loads
   int no_b;                                   // row products without the -b term
@@ -262,6 +278,13 @@ hipError_t launch_diagnostics(const AffineArgs &a, const DiagScratch &s,
 hipError_t launch_scaled_copy(const double *src, double *dst, int64_t n, const InstState *state,
                               int inst, hipStream_t st);
 
+struct FusedPlan {
+  std::vector<FusedTile> tiles;
+  std::vector<int64_t> part_first;            // 2 per instance
+  int64_t part_doubles = 0;
+};
+FusedPlan plan_fused(const std::vector<InstDesc> &inst);   // no tiles where it does not pay
+int64_t fused_slots_per_row();
 hipError_t launch_iteration_affine(const AffineArgs &a, hipStream_t st);
 // The affine step with conjugate gradients: scatter, r0, the solve, u.
 hipError_t launch_cg_affine(const AffineArgs &a, hipStream_t st);
