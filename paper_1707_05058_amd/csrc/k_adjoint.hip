@@ -11,8 +11,8 @@
 //                  Lb <- Lb - Wb / rho          (Daleckii-Krein, from V, theta)
 //   k_adj_scatter: ubar = seed + sum_k H_k^T Ub  (adjoint of the gather)
 //   affine stages: one KKT solve with b = 0: bhb = P ubar, ybar = multiplier
-//   k_adj_coord:   cbar -= bhb / rho;  bbar += ybar
-//   k_adj_gather:  Xb = H_k bhb;  Lb += H_k bhb / rho
+//   k_adj_coord_gather:  cbar -= bhb / rho;  bbar += ybar;
+//                  Xb = H_k bhb;  Lb += H_k bhb / rho
 // The eigenvectors and eigenvalues of each W_k come from a recomputation of
 // the segment since the last checkpoint (k_project stores them).
 #include "sdp_internal.h"
@@ -102,23 +102,36 @@ __global__ __launch_bounds__(NT) void k_adj_proj(AdjArgs a, const int32_t *__res
                                });
 }
 
+// Four lanes per coordinate share its clique entries, as in the forward scatter
+// (one thread walking the 50 entries of a shared coordinate: 20 us a call on 8
+// instances of 50 cliques of 24).
+constexpr int ADJ_LANES = 4;
+
 __global__ __launch_bounds__(256) void k_adj_scatter(AdjArgs a) {
-  const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (g >= a.ncoord) return;
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t g = e / ADJ_LANES;
+  const int q = (int)(e % ADJ_LANES);
+  if (g >= a.ncoord) return;               // whole lane groups leave together
+  double u = 0.0;
+  for (int64_t t = a.contrib_ptr[g] + q; t < a.contrib_ptr[g + 1]; t += ADJ_LANES)
+    u += a.Ub[a.contrib_idx[t]];
+#pragma unroll
+  for (int o = 1; o < ADJ_LANES; o <<= 1) u += __shfl_xor(u, o, 64);
+  if (q != 0) return;
   const int inst = a.coord_inst[g];
   const InstDesc d = a.inst[inst];
   const int64_t j = g - d.coord_off;
-  double u = 0.0;
   if (a.seed && j < d.nnz) {
-    u = a.seed[a.user_coord_off[inst] + j];
-    if (a.euclid) u /= a.w[g];
+    const double s = a.seed[a.user_coord_off[inst] + j];
+    u += a.euclid ? s / a.w[g] : s;
   }
-  for (int64_t t = a.contrib_ptr[g]; t < a.contrib_ptr[g + 1]; ++t) u += a.Ub[a.contrib_idx[t]];
   a.bhat_bar[g] = u;
   a.v_bar[g] = a.w[g] * u / a.D[g];
 }
 
-__global__ __launch_bounds__(256) void k_adj_coord(AdjArgs a) {
+// The cotangents of C and b (threads of coordinates and rows), and Xb, Lb of
+// the packed entries, in one launch.
+__global__ __launch_bounds__(256) void k_adj_coord_gather(AdjArgs a) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t < a.ncoord) {
     const int inst = a.coord_inst[t];
@@ -136,16 +149,13 @@ __global__ __launch_bounds__(256) void k_adj_coord(AdjArgs a) {
     const int64_t i = t - d.row_off;
     if (i < d.m) a.bbar[a.user_row_off[inst] + i] += a.y_bar[t];
   }
-}
-
-__global__ __launch_bounds__(256) void k_adj_gather(AdjArgs a) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= a.npk) return;
-  const int64_t g = a.blk_loc[e];
-  const int inst = a.coord_inst[g];
-  const double v = a.bhb[g];
-  a.Xb[e] = v;
-  a.Lb[e] += v / a.state[inst].rho;
+  if (t < a.npk) {
+    const int64_t g = a.blk_loc[t];
+    const int inst = a.coord_inst[g];
+    const double v = a.bhb[g];
+    a.Xb[t] = v;
+    a.Lb[t] += v / a.state[inst].rho;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_copy_user(const double *src, double *dst,
@@ -214,14 +224,14 @@ hipError_t launch_adj_projection(int precision, int N, const int32_t *list, int 
 int adjoint_max_bucket(int precision) { return precision == 1 ? 128 : 96; }
 
 hipError_t launch_adj_scatter(const AdjArgs &a, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_scatter, dim3((a.ncoord + 255) / 256), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_adj_scatter, dim3((a.ncoord * ADJ_LANES + 255) / 256), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_adj_coord_and_gather(const AdjArgs &a, hipStream_t st) {
-  const int64_t n = a.ncoord > a.nrow ? a.ncoord : a.nrow;
-  hipLaunchKernelGGL(k_adj_coord, dim3((n + 255) / 256), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_adj_gather, dim3((a.npk + 255) / 256), dim3(256), 0, st, a);
+  int64_t n = a.ncoord > a.nrow ? a.ncoord : a.nrow;
+  if (a.npk > n) n = a.npk;
+  hipLaunchKernelGGL(k_adj_coord_gather, dim3((n + 255) / 256), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -263,7 +263,10 @@ __global__ __launch_bounds__(COL_NT) void k_coldot(AffineArgs a) {
 // time: a member that has polled FU_SPIN times computes the missing parts
 // itself, with the same arithmetic, so the results do not depend on it.
 // Bound: HBM; 8 (rows + 2 groups) bytes per column instead of 16 rows.
-// FUSED_FIGURES
+// Measured, both products (two passes -> this and k_fused_reduce): 255 MB 75.7
+// -> 45.6 us (one pass at 6.0 TB/s), 769 MB of 12 uneven instances 241 -> 132 us,
+// 339 MB of 8 instances 118 -> 65 us, 101 MB 35 -> 25 us.  Two workgroups of half
+// the columns per unit: 255 MB 47.3 us, 769 MB 142 us.
 // ---------------------------------------------------------------------------
 constexpr int FU_NT = 512;                 // threads: one workgroup per unit
 constexpr int FU_K = 4;                    // pairs of columns per thread
@@ -271,7 +274,9 @@ constexpr int FU_R = 8;                    // rows at a time
 constexpr int FU_COLS = 2 * FU_NT * FU_K;  // most columns of a member
 constexpr int FU_MAXG = 16;                // most members of a cluster
 constexpr int FU_SPIN = 400;
-constexpr int64_t FUSED_MIN_BYTES = 1 << 20;
+// The two passes serve smaller matrices from the L2s (bands: 5.6 MB 10.8 us
+// against 11.2, 15.8 MB 12.9 against 12.7, 31 MB 19.1 against 12.4).
+constexpr int64_t FUSED_MIN_BYTES = 20 << 20;
 
 // Sum over each row of 16 lanes, the same in every lane of the row.
 __device__ inline double row16_sum(double v) {

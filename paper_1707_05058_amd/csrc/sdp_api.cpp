@@ -316,8 +316,9 @@ struct sdp_handle {
   int adj_T = 0, adj_ckpt = 0;
   double *d_ckpt = nullptr;              // [nseg][2][npk]: X, Lambda at segment starts
   int64_t ckpt_cap = 0;
-  void *d_eigbuf = nullptr;              // [ckpt][eig_total]
+  void *d_eigbuf = nullptr;              // (V, theta) records: [ckpt][eig_total], or [T] (eig_all)
   int64_t eigbuf_cap = 0;
+  bool eig_all = false;                  // the last forward kept every iteration's records
   double *d_Xb = nullptr, *d_Lb = nullptr, *d_Ub = nullptr;
   double *d_bhat_bar = nullptr, *d_v_bar = nullptr, *d_bhb = nullptr;
   double *d_r_bar = nullptr, *d_y1_bar = nullptr, *d_y_bar = nullptr, *d_zero_rows = nullptr;
@@ -390,29 +391,75 @@ void enqueue_sequence(sdp_handle *h, hipStream_t st, int64_t n) {
   for (int64_t i = 0; i < n; ++i) enqueue_iteration(h, st, fold && i > 0, fold && i + 1 < n);
 }
 
+// The Jacobi variant of the unrolled iterations for blocks of N: their solves
+// start cold, where the most threads per block are fastest at every number of
+// cliques measured (400 blocks of 24: 165 us with 64 threads, 85 with 256 in
+// FP32, 340 and 193 in FP64; 3000: 309 and 298, 958 and 719; 400 of 56: 679
+// with 256, 539 with 512).  -1 where no kernel has eigenvectors.
+int unrolled_variant(int precision, int N) {
+  int best = -1, best_nt = 0;
+  for (int v = 0; v < projection_variant_count(precision); ++v) {
+    int n, nt;
+    projection_variant_info(precision, v, &n, &nt);
+    if (n == N && projection_variant_kind(precision, v) == 0 && nt > best_nt) {
+      best = v;
+      best_nt = nt;
+    }
+  }
+  return best;
+}
+
 // One unrolled iteration (no stopping test); optionally stores (V, theta).
-void enqueue_unrolled_iteration(sdp_handle *h, hipStream_t st, void *eig) {
+// fold_prev: the scatter finishes the previous iteration (enqueue_iteration).
+void enqueue_unrolled_iteration(sdp_handle *h, hipStream_t st, void *eig, bool fold_prev,
+                                bool defer) {
   AffineArgs a = h->aff;
   a.params.no_stop = 1;
   a.ignore_done = 1;
+  if (fold_prev) a.res_blocks = (h->B + 7) / 8 * 8;
   ProjArgs p = h->proj;
   p.eig = eig;
   p.eig_off = h->d_eig_off;
   p.vw = nullptr;          // the reverse sweep recomputes segments: no cross-iteration state
   HIPCHK(launch_iteration_affine(a, st));
-  // always the Jacobi kernels (the sign-function lists of the plan take the
-  // Jacobi default of their block size): the recomputed segments record
-  // eigenvectors, and the first pass must compute the same iterates bit for
-  // bit, or the checkpoint spacing would change the result
+  // always the Jacobi kernels: the recomputed segments record eigenvectors,
+  // and the first pass must compute the same iterates bit for bit, or the
+  // checkpoint spacing would change the result
   for (size_t b = 0; b < h->bucket_size.size(); ++b) {
-    int v = h->bucket_size[b];
-    if (projection_variant_kind(h->precision, v) == 2)
-      v = projection_default_variant(h->precision, h->bucket_N[b]);
+    const int v = unrolled_variant(h->precision, h->bucket_N[b]);
     if (v < 0) fail(SDP_ERR_UNSUPPORTED, "no eigenvector kernel for this block size");
     HIPCHK(launch_admm_projection(h->precision, v, h->bucket_list[b], h->bucket_count[b], p, st));
   }
-  HIPCHK(launch_residual_reduce(a, st));
+  if (!defer) {
+    a.res_blocks = 0;
+    HIPCHK(launch_residual_reduce(a, st));
+  }
 }
+
+// Room for `records` iterations' (V, theta) records.
+bool reserve_eigbuf(sdp_handle *h, int64_t records, bool may_fail) {
+  const size_t esz = h->precision == SDP_FP32_EIG ? sizeof(float) : sizeof(double);
+  const int64_t need = records * std::max<int64_t>(h->eig_total, 1);
+  if (need <= h->eigbuf_cap) return true;
+  HIPCHK(hipStreamSynchronize(h->stream));
+  if (h->d_eigbuf) (void)hipFree(h->d_eigbuf);
+  h->d_eigbuf = nullptr;
+  h->eigbuf_cap = 0;
+  const hipError_t e = hipMalloc(&h->d_eigbuf, esz * need);
+  if (e != hipSuccess && may_fail) {
+    (void)hipGetLastError();
+    h->d_eigbuf = nullptr;
+    return false;
+  }
+  HIPCHK(e);
+  h->eigbuf_cap = need;
+  return true;
+}
+
+// The forward keeps every iteration's eigenvectors up to this many bytes (1.5%
+// of the card), which spares the reverse sweep the recomputation of the
+// segments; beyond it, checkpoints every ckpt_every iterations.
+constexpr int64_t EIG_ALL_BYTES = int64_t(4) << 30;
 
 // y = L^-T y1 for every row (with B = L^-1 A formed, the iteration keeps only y1).
 void ensure_y(sdp_handle *h) {
@@ -1803,8 +1850,12 @@ int sdp_unrolled_forward(sdp_handle *h, int32_t T, int32_t ckpt_every, double *u
     if (!h->adj_ready)
       fail(SDP_ERR_UNSUPPORTED, "unrolled differentiation takes cliques of up to 128 vertices in "
                                 "FP32 and 96 in FP64");
+    const size_t esz = h->precision == SDP_FP32_EIG ? sizeof(float) : sizeof(double);
+    h->adj_T = 0;
+    h->eig_all = (double)esz * h->eig_total * T <= (double)EIG_ALL_BYTES &&
+                 reserve_eigbuf(h, T, true);
     const int nseg = (T + ckpt_every - 1) / ckpt_every;
-    const int64_t need = (int64_t)nseg * 2 * std::max<int64_t>(h->npk, 1);
+    const int64_t need = h->eig_all ? 0 : (int64_t)nseg * 2 * std::max<int64_t>(h->npk, 1);
     if (need > h->ckpt_cap) {
       HIPCHK(hipStreamSynchronize(h->stream));
       if (h->d_ckpt) (void)hipFree(h->d_ckpt);
@@ -1816,14 +1867,15 @@ int sdp_unrolled_forward(sdp_handle *h, int32_t T, int32_t ckpt_every, double *u
     reset_state(h);
     const int64_t np = std::max<int64_t>(h->npk, 1);
     for (int t = 0; t < T; ++t) {
-      if (t % ckpt_every == 0) {
+      if (!h->eig_all && t % ckpt_every == 0) {
         double *slot = h->d_ckpt + (int64_t)(t / ckpt_every) * 2 * np;
         HIPCHK(hipMemcpyAsync(slot, h->proj.X, sizeof(double) * h->npk, hipMemcpyDeviceToDevice,
                               h->stream));
         HIPCHK(hipMemcpyAsync(slot + np, h->proj.Lam, sizeof(double) * h->npk,
                               hipMemcpyDeviceToDevice, h->stream));
       }
-      enqueue_unrolled_iteration(h, h->stream, nullptr);
+      void *rec = h->eig_all ? (char *)h->d_eigbuf + esz * (size_t)t * h->eig_total : nullptr;
+      enqueue_unrolled_iteration(h, h->stream, rec, t > 0, t + 1 < T);
     }
     if (u_out)
       HIPCHK(launch_copy_user(h->aff.u, u_out, h->d_desc, h->aff.coord_inst, h->d_user_coord_off,
@@ -1861,15 +1913,7 @@ int sdp_vjp(sdp_handle *h, const double *u_bar, double *c_bar, double *b_bar, in
     }
     const int T = h->adj_T, ck = h->adj_ckpt;
     const size_t esz = h->precision == SDP_FP32_EIG ? sizeof(float) : sizeof(double);
-    const int64_t eneed = (int64_t)ck * std::max<int64_t>(h->eig_total, 1);
-    if (eneed > h->eigbuf_cap) {
-      HIPCHK(hipStreamSynchronize(h->stream));
-      if (h->d_eigbuf) (void)hipFree(h->d_eigbuf);
-      h->d_eigbuf = nullptr;
-      h->eigbuf_cap = 0;
-      HIPCHK(hipMalloc(&h->d_eigbuf, esz * eneed));
-      h->eigbuf_cap = eneed;
-    }
+    if (!h->eig_all) reserve_eigbuf(h, ck, false);
     HIPCHK(hipMemsetAsync(h->d_Xb, 0, sizeof(double) * h->npk, h->stream));
     HIPCHK(hipMemsetAsync(h->d_Lb, 0, sizeof(double) * h->npk, h->stream));
     HIPCHK(hipMemsetAsync(c_bar, 0, sizeof(double) * h->user_ncoord, h->stream));
@@ -1918,17 +1962,20 @@ int sdp_vjp(sdp_handle *h, const double *u_bar, double *c_bar, double *b_bar, in
     ra.y = h->d_y_bar;
     ra.u = h->d_bhb;
     const int64_t np = std::max<int64_t>(h->npk, 1);
-    const int nseg = (T + ck - 1) / ck;
+    const int seg_len = h->eig_all ? T : ck, nseg = (T + seg_len - 1) / seg_len;
     for (int seg = nseg - 1; seg >= 0; --seg) {
-      const int t0 = seg * ck, t1 = std::min(T, t0 + ck);
-      const double *slot = h->d_ckpt + (int64_t)seg * 2 * np;
-      HIPCHK(hipMemcpyAsync(h->proj.X, slot, sizeof(double) * h->npk, hipMemcpyDeviceToDevice,
-                            h->stream));
-      HIPCHK(hipMemcpyAsync(h->proj.Lam, slot + np, sizeof(double) * h->npk,
-                            hipMemcpyDeviceToDevice, h->stream));
-      for (int t = t0; t < t1; ++t)
-        enqueue_unrolled_iteration(h, h->stream,
-                                   (char *)h->d_eigbuf + esz * (size_t)(t - t0) * h->eig_total);
+      const int t0 = seg * seg_len, t1 = std::min(T, t0 + seg_len);
+      if (!h->eig_all) {
+        const double *slot = h->d_ckpt + (int64_t)seg * 2 * np;
+        HIPCHK(hipMemcpyAsync(h->proj.X, slot, sizeof(double) * h->npk, hipMemcpyDeviceToDevice,
+                              h->stream));
+        HIPCHK(hipMemcpyAsync(h->proj.Lam, slot + np, sizeof(double) * h->npk,
+                              hipMemcpyDeviceToDevice, h->stream));
+        for (int t = t0; t < t1; ++t)
+          enqueue_unrolled_iteration(h, h->stream,
+                                     (char *)h->d_eigbuf + esz * (size_t)(t - t0) * h->eig_total,
+                                     t > t0, t + 1 < t1);
+      }
       for (int t = t1 - 1; t >= t0; --t) {
         g.eig = (const char *)h->d_eigbuf + esz * (size_t)(t - t0) * h->eig_total;
         g.seed = (t == T - 1) ? u_bar : nullptr;
