@@ -78,33 +78,60 @@ __device__ inline double cratio(double num, double a, double b) {
   return num == 0.0 ? 0.0 : INFINITY;
 }
 
-// nu = omega_1 - omega_2 zeta with omega = u + v; in set-up mode nu = zeta
-// = (c, 0, -b, 0) (for M^-1 zeta).
-__global__ __launch_bounds__(256) void k_hsde_form_nu(HsdeArgs h, int setup) {
+// Set-up: nu = zeta = (c, 0, -b, 0) (for M^-1 zeta).
+__global__ __launch_bounds__(256) void k_hsde_zeta(HsdeArgs h) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < h.ncoord) {
-    const int inst = h.coord_inst[t];
-    if (setup) h.nx[t] = h.c[t];
-    else if (!h.state[inst].done) h.nx[t] = h.ux[t] - h.hs[inst].w2 * h.c[t];
-  }
+  if (t < h.ncoord) h.nx[t] = h.c[t];
   if (t < h.npk) {
-    const int inst = h.coord_inst[h.blk_loc[t]];
-    if (setup) {
-      h.ns[t] = 0.0;
-      h.nt[t] = 0.0;
-    } else if (!h.state[inst].done) {
-      h.ns[t] = h.us[t] + h.vz[t];
-      h.nt[t] = h.ut[t];
-    }
+    h.ns[t] = 0.0;
+    h.nt[t] = 0.0;
   }
-  if (t < h.nrow) {
-    const int inst = h.row_inst[t];
-    if (setup) h.ny[t] = -h.b[t];
-    else if (!h.state[inst].done) h.ny[t] = h.uy[t] + h.hs[inst].w2 * h.b[t];
+  if (t < h.nrow) h.ny[t] = -h.b[t];
+}
+
+// The iteration's start in one launch: nu = omega_1 - omega_2 zeta with omega =
+// u + v on the blocks and rows (workgroups from nbx on), and x' = nu_x +
+// H^T (nu_s + nu_t) / 2, v = w x' / P on the coordinates, which form nu_s + nu_t
+// from u and v again, so that neither part waits for the other.
+__global__ __launch_bounds__(256) void k_hsde_start(HsdeArgs h, int nbx) {
+  if ((int)blockIdx.x >= nbx) {
+    const int64_t t = (int64_t)(blockIdx.x - nbx) * 256 + threadIdx.x;
+    if (t < h.npk) {
+      const int inst = h.coord_inst[h.blk_loc[t]];
+      if (!h.state[inst].done) {
+        h.ns[t] = h.us[t] + h.vz[t];
+        h.nt[t] = h.ut[t];
+      }
+    }
+    if (t < h.nrow) {
+      const int inst = h.row_inst[t];
+      if (!h.state[inst].done) h.ny[t] = h.uy[t] + h.hs[inst].w2 * h.b[t];
+    }
+    return;
+  }
+  const int q8 = nbx / 8, r8 = nbx % 8, x8 = blockIdx.x % 8;
+  const int64_t g = (int64_t)(x8 * q8 + min(x8, r8) + blockIdx.x / 8) * 256 + threadIdx.x;
+  const int64_t j = g / HS_LANES;
+  const int q = (int)(g % HS_LANES);
+  if (j >= h.ncoord) return;
+  const int inst = h.coord_inst[j];
+  if (h.state[inst].done) return;
+  double acc = 0.0;
+  const int64_t t1 = h.contrib_ptr[j + 1];
+  for (int64_t t = h.contrib_ptr[j] + q; t < t1; t += HS_LANES) {
+    const int32_t e = h.contrib_idx[t];
+    acc += (h.us[e] + h.vz[e]) + h.ut[e];
+  }
+#pragma unroll
+  for (int o = 1; o < HS_LANES; o <<= 1) acc += __shfl_xor(acc, o, 64);
+  if (q == 0) {
+    const double x = (h.ux[j] - h.hs[inst].w2 * h.c[j]) + 0.5 * acc;
+    h.xp[j] = x;
+    h.v[j] = h.w[j] * x / h.P[j];
   }
 }
 
-// x' = nu_x + H^T (nu_s + nu_t) / 2 and v = w x' / P (four lanes per coordinate,
+// Set-up: x' = nu_x + H^T (nu_s + nu_t) / 2 and v = w x' / P (four lanes per coordinate,
 // fixed butterfly; workgroups numbered contiguously per XCD).
 __global__ __launch_bounds__(256) void k_hsde_xprime(HsdeArgs h, const double *nx, const double *ns,
                                                      const double *nt) {
@@ -211,42 +238,39 @@ __global__ __launch_bounds__(256) void k_hsde_zs_partials(HsdeArgs h) {
   }
 }
 
-// One workgroup per instance: zeta^T sigma from the wave partials (each
-// thread a strided share, summed over the workgroup in a fixed order), then
-// f = kz zeta^T sigma, u_hat_tau = omega_2 + f, tau = max(0, u_hat_tau -
-// kappa), kappa -= u_hat_tau - tau.
-__global__ __launch_bounds__(256) void k_hsde_scalars(HsdeArgs h) {
-  __shared__ double red[4];
-  const int inst = blockIdx.x;
-  if (h.state[inst].done) return;   // uniform per workgroup
+// f = kz zeta^T sigma of instance `inst` from the wave partials, formed by a
+// whole wave in a fixed order (every wave of the instance forms the same).
+__device__ inline double hsde_f(const HsdeArgs &h, int inst) {
   const InstDesc d = h.inst[inst];
+  const int l = threadIdx.x & 63;
   double zs = 0.0;
-  for (int64_t q = (d.coord_off >> 6) + threadIdx.x; q < (d.coord_off + d.ld) >> 6; q += 256)
+  for (int64_t q = (d.coord_off >> 6) + l; q < (d.coord_off + d.ld) >> 6; q += 64)
     zs += h.cw_part[q * WSLOT];
-  for (int64_t q = (d.row_off >> 6) + threadIdx.x; q < (d.row_off + d.ldm) >> 6; q += 256)
+  for (int64_t q = (d.row_off >> 6) + l; q < (d.row_off + d.ldm) >> 6; q += 64)
     zs += h.rw_part[q * WSLOT];
-  zs = block_total<256>(zs, red);
-  if (threadIdx.x != 0) return;
-  HsdeState &s = h.hs[inst];
-  const double f = s.kz * zs;
-  const double uhat_tau = s.w2 + f;
-  const double tau = uhat_tau - s.kappa > 0.0 ? uhat_tau - s.kappa : 0.0;
-  s.f = f;
-  s.kappa = s.kappa - uhat_tau + tau;
-  s.tau = tau;
-  s.w2 = s.tau + s.kappa;
+  return h.hs[inst].kz * wsum(zs);
 }
 
-// u_x = sigma_x - f mz_x, u_y = -g - f mz_y, A W u_x = nu_y + g - f A W mz_x,
-// with their wave partial sums.
+// f and tau = max(0, u_hat_tau - kappa) with u_hat_tau = omega_2 + f, in every
+// wave (a launch of its own for these scalars took 4.5 us; kappa and omega_2,
+// which the waves still read here, are updated by k_hsde_finish); u_x =
+// sigma_x - f mz_x, u_y = -g - f mz_y, A W u_x = nu_y + g - f A W mz_x, with
+// their wave partial sums.
 __global__ __launch_bounds__(256) void k_hsde_apply(HsdeArgs h) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int lane = threadIdx.x & 63;
-  if (t < h.ncoord) {
+  if (t < h.ncoord) {                                  // uniform per wave
     const int inst = h.coord_inst[t];
     double ctx = 0.0;
     if (!h.state[inst].done) {
-      const double ux = h.sx[t] - h.hs[inst].f * h.mzx[t];
+      const double f = hsde_f(h, inst);
+      HsdeState &s = h.hs[inst];
+      if (t == h.inst[inst].coord_off) {
+        const double uhat_tau = s.w2 + f;
+        s.f = f;
+        s.tau = uhat_tau - s.kappa > 0.0 ? uhat_tau - s.kappa : 0.0;
+      }
+      const double ux = h.sx[t] - f * h.mzx[t];
       h.ux[t] = ux;
       ctx = h.w[t] * h.c[t] * ux;
     }
@@ -257,13 +281,16 @@ __global__ __launch_bounds__(256) void k_hsde_apply(HsdeArgs h) {
     const int inst = h.row_inst[t];
     double bty = 0.0, ax2 = 0.0, rp2 = 0.0;
     if (!h.state[inst].done) {
+      const double f = hsde_f(h, inst);
       const HsdeState &s = h.hs[inst];
-      const double uy = -h.g[t] - s.f * h.mzy[t];
+      const double uhat_tau = s.w2 + f;
+      const double tau = uhat_tau - s.kappa > 0.0 ? uhat_tau - s.kappa : 0.0;
+      const double uy = -h.g[t] - f * h.mzy[t];
       h.uy[t] = uy;
       bty = h.b[t] * uy;
-      const double aux = h.ny[t] + h.g[t] - s.f * h.az[t];
+      const double aux = h.ny[t] + h.g[t] - f * h.az[t];
       ax2 = aux * aux;
-      const double rp = aux - s.tau * h.b[t];
+      const double rp = aux - tau * h.b[t];
       rp2 = rp * rp;
     }
     bty = wsum(bty);
@@ -354,6 +381,9 @@ __global__ __launch_bounds__(256) void k_hsde_finish(HsdeArgs h) {
   for (int q = 0; q < 7; ++q) S[q] = tot[6 + q];
   s.ctx = ctx;
   s.bty = bty;
+  // kappa -= u_hat_tau - tau (HsdeStep3), omega_2 of the next iteration
+  s.kappa = s.kappa - (s.w2 + s.f) + s.tau;
+  s.w2 = s.tau + s.kappa;
   const SolverParams &P = h.params;
   const int it = st.iter + 1;
   const double tau = s.tau;
@@ -418,9 +448,11 @@ int64_t max3(int64_t a, int64_t b, int64_t c) { return a > b ? (a > c ? a : c) :
 
 }  // namespace
 
-hipError_t launch_hsde_form_nu(const HsdeArgs &h, hipStream_t st) {
-  const int64_t n = max3(h.ncoord, h.npk, h.nrow);
-  hipLaunchKernelGGL(k_hsde_form_nu, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, h, 0);
+hipError_t launch_hsde_start(const HsdeArgs &h, hipStream_t st) {
+  const int nbx = (int)((h.ncoord * HS_LANES + 255) / 256);
+  const int64_t n = h.npk > h.nrow ? h.npk : h.nrow;
+  hipLaunchKernelGGL(k_hsde_start, dim3((unsigned)(nbx + (n + 255) / 256)), dim3(256), 0, st, h,
+                     nbx);
   return hipGetLastError();
 }
 
@@ -443,7 +475,7 @@ hipError_t launch_hsde_setup_finish(const HsdeArgs &h, hipStream_t st) {
 
 hipError_t launch_hsde_setup_nu(const HsdeArgs &h, hipStream_t st) {
   const int64_t n = max3(h.ncoord, h.npk, h.nrow);
-  hipLaunchKernelGGL(k_hsde_form_nu, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, h, 1);
+  hipLaunchKernelGGL(k_hsde_zeta, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, h);
   return hipGetLastError();
 }
 
@@ -451,7 +483,6 @@ hipError_t launch_hsde_update(const HsdeArgs &h, hipStream_t st) {
   const int64_t n = h.ncoord > h.nrow ? h.ncoord : h.nrow;
   const unsigned nb = (unsigned)((n + 255) / 256);
   hipLaunchKernelGGL(k_hsde_zs_partials, dim3(nb), dim3(256), 0, st, h);
-  hipLaunchKernelGGL(k_hsde_scalars, dim3(h.batch), dim3(256), 0, st, h);
   hipLaunchKernelGGL(k_hsde_apply, dim3(nb), dim3(256), 0, st, h);
   return hipGetLastError();
 }

@@ -274,6 +274,8 @@ struct sdp_handle {
   void *d_vw = nullptr;                  // warm-start bases (precision of the eigen-solve)
   int32_t *d_t_rows_all = nullptr;       // (inst, row) over every row
   int n_t_rows_all = 0;
+  int32_t *d_t_rows_dense = nullptr;     // (inst, row) over the rows of dense instances
+  int n_t_rows_dense = 0;
   double *d_ytmp = nullptr;              // row-space scratch for the scaled multiplier
   double *d_utmp = nullptr;              // coordinate scratch (Algorithm 2: -rho x)
   // affine step by conjugate gradients (no factor)
@@ -483,6 +485,20 @@ void compute_bp(sdp_handle *h) {
   HIPCHK(launch_affine_stage(a, 2, h->stream));
 }
 
+// Stage s (1 to 4) of Algorithm 3's inner solve; with B = L^-1 A the first
+// begins with bp = L^-1 nu_y on the dense instances' rows.
+void hsde_affine(sdp_handle *h, const AffineArgs &a, int s, hipStream_t st) {
+  if (s == 1 && a.Bm) {
+    AffineArgs q = a;
+    q.r = const_cast<double *>(a.b);
+    q.y1 = const_cast<double *>(a.bp);
+    q.t_rows = h->d_t_rows_dense;
+    q.n_t_rows = h->n_t_rows_dense;
+    HIPCHK(launch_affine_stage(q, 2, st));
+  }
+  HIPCHK(launch_affine_stage(a, s, st));
+}
+
 // Algorithm 3 set-up: buffers, then M^-1 zeta by one inner solve of nu = zeta
 // = (c, 0, -b, 0) through the same kernels as the iteration.
 void setup_hsde(sdp_handle *h, const std::vector<double> &D) {
@@ -557,7 +573,7 @@ void setup_hsde(sdp_handle *h, const std::vector<double> &D) {
   as.ignore_done = 1;
   HIPCHK(launch_hsde_setup_nu(g, h->stream));
   HIPCHK(launch_hsde_xprime(g, g.nx, g.ns, g.nt, h->stream));
-  for (int stg = 1; stg <= 4; ++stg) HIPCHK(launch_affine_stage(as, stg, h->stream));
+  for (int stg = 1; stg <= 4; ++stg) hsde_affine(h, as, stg, h->stream);
   HIPCHK(launch_hsde_setup_finish(g, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
   g.ignore_done = 0;
@@ -565,9 +581,8 @@ void setup_hsde(sdp_handle *h, const std::vector<double> &D) {
 
 void enqueue_hsde_iteration(sdp_handle *h, hipStream_t st) {
   const HsdeArgs &g = h->hsa;
-  HIPCHK(launch_hsde_form_nu(g, st));
-  HIPCHK(launch_hsde_xprime(g, g.nx, g.ns, g.nt, st));
-  for (int stg = 1; stg <= 4; ++stg) HIPCHK(launch_affine_stage(h->aff, stg, st));
+  HIPCHK(launch_hsde_start(g, st));
+  for (int stg = 1; stg <= 4; ++stg) hsde_affine(h, h->aff, stg, st);
   HIPCHK(launch_hsde_update(g, st));
   enqueue_projections(h, h->proj, st);
   HIPCHK(launch_hsde_finish(g, st));
@@ -914,10 +929,12 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     const int R = pick_r(dense_rows);
     const int CW = affine_col_tile_width();
     std::vector<int32_t> row_tiles, col_tiles, t_rows, csr_rows, csc_cols, syrk_tiles, syrk_rows;
-    std::vector<int32_t> t_rows_all, b_tiles;
+    std::vector<int32_t> t_rows_all, t_rows_dense, b_tiles;
     for (int i = 0; i < batch; ++i) {
       const HostInst &hi = H[i];
       for (int r = 0; r < hi.m; ++r) { t_rows_all.push_back(i); t_rows_all.push_back(r); }
+      if (hi.fmt == SDP_A_DENSE)
+        for (int r = 0; r < hi.m; ++r) { t_rows_dense.push_back(i); t_rows_dense.push_back(r); }
       if (hi.fmt != SDP_A_DENSE)
         for (int r = 0; r < hi.m; ++r) { t_rows.push_back(i); t_rows.push_back(r); }
       if (hi.fmt == SDP_A_DENSE) {
@@ -1053,23 +1070,32 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     h->d_t_rows_all = dev_upload(t_rows_all, own);
     h->n_t_rows_all = (int)(t_rows_all.size() / 2);
     h->d_ytmp = dev_zeros<double>(row, own);
+    const FusedPlan fp = d_A && !cg ? plan_fused(h->desc) : FusedPlan();
     if (opt.algorithm == SDP_ALG_HSDE) {
-      // the embedding solves with right-hand sides that change every
-      // iteration on both sides of the factor: keep A and both triangular passes
-      a.t_rows = a.t3_rows = h->d_t_rows_all;
-      a.n_t_rows = a.n_t3_rows = h->n_t_rows_all;
-    } else if (d_A && !cg) {
+      // the embedding needs g = L^-T y1 itself on every row; its right-hand
+      // side changes every iteration on both sides of the factor, so L^-1
+      // nu_y is formed in the iteration (hsde_affine), and B pays only with
+      // the fused pass
+      a.t3_rows = h->d_t_rows_all;
+      a.n_t3_rows = h->n_t_rows_all;
+      if (fp.tiles.empty()) {
+        a.t_rows = h->d_t_rows_all;
+        a.n_t_rows = h->n_t_rows_all;
+      }
+    }
+    if (d_A && !cg && (opt.algorithm != SDP_ALG_HSDE || !fp.tiles.empty())) {
       a.Bm = dev_zeros<double>(aoff, own);
       a.bp = dev_zeros<double>(row, own);
-      const FusedPlan fp = plan_fused(h->desc);
-      if (!fp.tiles.empty()) {
-        a.fu_tiles = dev_upload(fp.tiles, own);
-        a.fu_ntiles = (int)fp.tiles.size();
-        a.fu_slots = dev_zeros<unsigned long long>(fused_slots_per_row() * row, own);
-        a.fu_tag = dev_upload(std::vector<uint32_t>(1, 1u), own);   // (cleared slots: tag 0)
-        a.fu_part = dev_zeros<double>(fp.part_doubles, own);
-        a.fu_part_first = dev_upload(fp.part_first, own);
-      }
+    }
+    if (!fp.tiles.empty()) {
+      h->d_t_rows_dense = dev_upload(t_rows_dense, own);
+      h->n_t_rows_dense = (int)(t_rows_dense.size() / 2);
+      a.fu_tiles = dev_upload(fp.tiles, own);
+      a.fu_ntiles = (int)fp.tiles.size();
+      a.fu_slots = dev_zeros<unsigned long long>(fused_slots_per_row() * row, own);
+      a.fu_tag = dev_upload(std::vector<uint32_t>(1, 1u), own);   // (cleared slots: tag 0)
+      a.fu_part = dev_zeros<double>(fp.part_doubles, own);
+      a.fu_part_first = dev_upload(fp.part_first, own);
     }
     a.csr_rows = dev_upload(csr_rows, own);
     a.n_csr_rows = (int)(csr_rows.size() / 2);
@@ -1766,10 +1792,9 @@ int sdp_time_stages(sdp_handle *h, int32_t n_iter, double *ms) {
         for (int it = 0; it < n_iter; ++it) {
           if (h->hsde) {   // 0 nu and x', 1-4 the inner solve, 5 update + projections, 6 residuals
             if (s == 0) {
-              HIPCHK(launch_hsde_form_nu(h->hsa, h->stream));
-              HIPCHK(launch_hsde_xprime(h->hsa, h->hsa.nx, h->hsa.ns, h->hsa.nt, h->stream));
+              HIPCHK(launch_hsde_start(h->hsa, h->stream));
             } else if (s < 5) {
-              HIPCHK(launch_affine_stage(h->aff, s, h->stream));
+              hsde_affine(h, h->aff, s, h->stream);
             } else if (s == 5) {
               HIPCHK(launch_hsde_update(h->hsa, h->stream));
               enqueue_projections(h, h->proj, h->stream);

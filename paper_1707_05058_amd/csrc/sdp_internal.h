@@ -360,9 +360,10 @@ struct HsdeArgs {
   double *hist;
 };
 
-// nu = u + v - (u_tau + v_kappa) zeta on every space (coordinates, blocks, rows)
-hipError_t launch_hsde_form_nu(const HsdeArgs &h, hipStream_t st);
-// x' = nu_x + H^T (nu_s + nu_t) / 2 and v = w x' / P on the coordinates
+// nu = u + v - (u_tau + v_kappa) zeta on the blocks and rows, and x' = nu_x +
+// H^T (nu_s + nu_t) / 2, v = w x' / P on the coordinates
+hipError_t launch_hsde_start(const HsdeArgs &h, hipStream_t st);
+// set-up: x' and v from given nu
 hipError_t launch_hsde_xprime(const HsdeArgs &h, const double *nx, const double *ns,
                               const double *nt, hipStream_t st);
 // set-up: M^-1 zeta from the inner solve of nu = zeta, kz and the norms
