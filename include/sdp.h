@@ -150,7 +150,7 @@ typedef struct {
                                    otherwise the Jacobi sweeps continue from the refined
                                    basis.  A clique whose attempts keep failing is projected
                                    by the matrix sign function and tries again only in the
-                                   iterations 32, 64, 128, 256, 512 and every 512th after
+                                   iterations 64, 128, 256, 512 and every 512th after
                                    that.  The
                                    result is P+(W) to the sweep tolerance either way.  With
                                    projection_method = 0 those blocks then take the scalar

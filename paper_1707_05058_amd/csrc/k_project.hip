@@ -47,8 +47,8 @@ constexpr int DEC_MIN_N = 64;
 // When a clique takes the decoupling: one double per clique (its partial-sum
 // slot 7), 64 times the iterations since the record was cleared plus m.  m = 0:
 // the sign function projects it (k_sign_big, launched on the list before the
-// decoupling kernel), except in the probe iterations 32, 64, 128, ... 512 and
-// every 512th after that.  m = 1 + n: the last n attempts succeeded (n counts
+// decoupling kernel), except in the probe iterations 64, 128, 256, 512 and every
+// 512th after that.  m = 1 + n: the last n attempts succeeded (n counts
 // to LONG).  An attempt that fails is finished by the Jacobi sweeps, which
 // leave a fresh basis; the clique tries again in the next iteration after a
 // probe or after LONG successes, else it goes back to the sign function.
@@ -58,7 +58,9 @@ constexpr int DEC_MIN_N = 64;
 // every time (or back-off waits that end at different times, so that some
 // clique sweeps in most iterations) cost 560-870 us per iteration on such
 // instances (now 220-430).  The probes are the same iterations for every
-// clique of an instance, so that their sweeps coincide.
+// clique of an instance, so that their sweeps coincide; the first, whose sweeps
+// start from the identity (3.5 ms for blocks of 128), pays after some 50
+// decoupled iterations, so a short solve does without.
 struct DecState {
   static constexpr int LONG = 31;
   int64_t it;
@@ -67,7 +69,7 @@ struct DecState {
   __device__ explicit DecState(double v) {
     it = (int64_t)v >> 6;
     n = (int)((int64_t)v & 63) - 1;
-    probe = it >= 32 && (it % 512 == 0 || (it < 512 && (it & (it - 1)) == 0));
+    probe = it >= 64 && (it % 512 == 0 || (it < 512 && (it & (it - 1)) == 0));
   }
   __device__ bool sign() const { return n < 0 && !probe; }
   __device__ double after_sign() const { return (double)((it + 1) * 64); }

@@ -930,6 +930,16 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     const int CW = affine_col_tile_width();
     std::vector<int32_t> row_tiles, col_tiles, t_rows, csr_rows, csc_cols, syrk_tiles, syrk_rows;
     std::vector<int32_t> t_rows_all, t_rows_dense, b_tiles;
+    int csr_per = 1;
+    {
+      int64_t rows = 0, nnz = 0;
+      for (int i = 0; i < batch; ++i) {
+        if (H[i].fmt == SDP_A_DENSE) continue;
+        rows += H[i].m;
+        nnz += inst[i].a_rowptr[inst[i].m];
+      }
+      csr_per = affine_csr_rows_per_wave(rows, nnz);
+    }
     for (int i = 0; i < batch; ++i) {
       const HostInst &hi = H[i];
       for (int r = 0; r < hi.m; ++r) { t_rows_all.push_back(i); t_rows_all.push_back(r); }
@@ -949,10 +959,8 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
             syrk_tiles.push_back(i); syrk_tiles.push_back(ti); syrk_tiles.push_back(tj);
           }
       } else {
-        for (int r = 0; r < hi.m; ++r) {
-          csr_rows.push_back(i); csr_rows.push_back(r);
-          syrk_rows.push_back(i); syrk_rows.push_back(r);
-        }
+        for (int r = 0; r < hi.m; r += csr_per) { csr_rows.push_back(i); csr_rows.push_back(r); }
+        for (int r = 0; r < hi.m; ++r) { syrk_rows.push_back(i); syrk_rows.push_back(r); }
         for (int cc = 0; cc < hi.ld; cc += affine_csc_tile_width()) {
           csc_cols.push_back(i);
           csc_cols.push_back(cc);
@@ -1099,6 +1107,7 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     }
     a.csr_rows = dev_upload(csr_rows, own);
     a.n_csr_rows = (int)(csr_rows.size() / 2);
+    a.csr_per = csr_per;
     a.csc_cols = dev_upload(csc_cols, own);
     a.n_csc_cols = (int)(csc_cols.size() / 2);
     double *d_part = dev_zeros<double>((size_t)cl * NPART, own);

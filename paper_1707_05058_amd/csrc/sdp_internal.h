@@ -229,7 +229,8 @@ struct AffineArgs {
   const int32_t *col_tiles; int n_col_tiles;
   const int32_t *t_rows; int n_t_rows;      // (inst, row) per wave for T r
   const int32_t *t3_rows; int n_t3_rows;    // (inst, row) per wave for T^T y1
-  const int32_t *csr_rows; int n_csr_rows;   // (inst, row) pairs for CSR instances
+  const int32_t *csr_rows; int n_csr_rows;   // (inst, first row) per wave for CSR instances
+  int csr_per;                               // rows per wave
   const int32_t *csc_cols; int n_csc_cols;   // (inst, col-chunk) pairs for CSR instances
   // residual partials
   const double *part;
@@ -379,6 +380,7 @@ hipError_t launch_hsde_solution(const HsdeArgs &h, double *x_out, double *y_out,
 
 int affine_col_tile_width();
 int affine_csc_tile_width();   // columns per workgroup of the sparse transposed product
+int affine_csr_rows_per_wave(int64_t rows, int64_t nnz);
 int affine_max_rows_per_tile();
 
 // ----------------------------------------------------------------------------
