@@ -552,9 +552,12 @@ __global__ __launch_bounds__(256) void k_csr_rowdot(AffineArgs a) {
     int32_t col[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int64_t e = t[r] < t1[r] ? t[r] : t1[r] - 1;   // (some entry of A: read, not used)
-      val[r] = a.a_val[e < 0 ? 0 : e];
-      col[r] = a.a_col[e < 0 ? 0 : e];
+      // (lanes past the row's end read A's first entry, which is not used: the
+      // column of a foreign entry may lie outside this instance)
+      const bool in = t[r] < t1[r];
+      const int64_t e = in ? t[r] : 0;
+      val[r] = a.a_val[e];
+      col[r] = in ? a.a_col[e] : 0;
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
