@@ -382,9 +382,10 @@ int sdp_unrolled_forward(sdp_handle *h, int32_t T, int32_t ckpt_every, double *u
  * layout).  With euclidean = 0 the cotangents of u and c are taken w.r.t. the
  * Frobenius inner product of the symmetric matrices (off-diagonal coordinates
  * weighted by 2); with euclidean = 1 w.r.t. the plain dot product of the
- * compact vectors (what an autodiff framework uses).  Segments between
- * checkpoints are recomputed forward, storing each projection's eigenvectors
- * (FP32 in the SDP_FP32_EIG form), then reversed; the projection adjoints run
+ * compact vectors (what an autodiff framework uses).  The forward keeps each
+ * projection's eigenvectors (FP32 in the SDP_FP32_EIG form) where all of them
+ * fit in 4 GiB; otherwise the segments between checkpoints are recomputed
+ * forward, storing them, then reversed.  The projection adjoints run
  * on the matrix cores for cliques of up to 128 vertices in FP32 and 96 in
  * FP64 (larger ones: sdp_unrolled_forward returns SDP_ERR_UNSUPPORTED).  The
  * handle's iterate is unspecified afterwards (call

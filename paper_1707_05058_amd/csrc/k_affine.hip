@@ -7,15 +7,17 @@
 //   y    = L^-T (L^-1 r)   with L^-1, L^-T cached               (k_trmv_wave)
 //   u    = (bhat - A^T y) / D                                   (k_coldot)
 // For dense A the forward substitution is folded into B = L^-1 A at setup:
-//   y1   = B (w bhat / D) - L^-1 b                              (k_rowdot)
+//   y1   = B (w bhat / D) - L^-1 b                     (k_fused or k_rowdot)
 //   u    = (bhat - B^T y1) / D       (A^T y = A^T L^-T y1)      (k_coldot)
 // and y = L^-T y1 is formed only when the multiplier is asked for.
 // plus the per-instance residual reduction, stopping test and adaptive
 // penalty (k_residual_reduce).  Every kernel reads the instance's `done`
 // flag first, so a converged instance is frozen at its stopping iterate.
 //
-// All of these passes stream HBM: A is read twice per iteration (row-wise,
-// then column-wise) and the factor twice; vectors are small and L2-resident.
+// All of these passes stream HBM: B is read once per iteration where it is
+// large (k_fused does both products, k_fused_reduce adds its column sums) and
+// twice where the caches hold it, a sparse A twice (row-wise, then column-
+// wise), and the factor twice; vectors are small and L2-resident.
 // Reductions use a fixed order, so results are bitwise reproducible.
 #include "sdp_internal.h"
 

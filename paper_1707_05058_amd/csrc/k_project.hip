@@ -1553,17 +1553,16 @@ void sign_schedule(double tol, int n, int *k1_out, int *k2_out) {
   *k2_out = it->second.second;
 }
 
-// The plan the kernels run: sign_schedule's worst case, and for every count k
-// of fast steps after which ||I - X^2||_F <= SIGN_THETA was seen the
-// Newton-Schulz steps that finish the iteration after one more fast step.
-// There every eigenvalue satisfies |1 - x_k^2| <= SIGN_THETA, so only the
-// starting points x_0 of the grid whose scalar iterates do are left, and the
-// bound 2 sqrt(n - 1) max e <= tol of sign_schedule is taken over those, with
-// tol / 4: a quarter costs no step on most spectra (22.4 products instead of
-// 21.9 for FP32 blocks of 16) and keeps stopping early from using the budget
-// up.
-// (The first step scales X0 by c >= 1 with |c X0| <= SIGN_X_MAX: an eigenvalue
-// delta starts at x_0 = c delta, and |x_0| |1 - s| / 2 bounds its error.)
+// The plan the kernels run: sign_schedule's fast steps with the finishing
+// steps its worst case needs, and for every count k of fast steps after which
+// ||I - X^2||_F <= SIGN_THETA was seen the finishing steps that are left after
+// one more fast step.  There every eigenvalue satisfies |1 - x_k^2| <=
+// SIGN_THETA, so only the starting points x_0 of the grid whose scalar
+// iterates do are left, and the bound 2 sqrt(n - 1) max e <= tol of
+// sign_schedule is taken over those, with tol / 3, which keeps stopping early
+// from using the budget up.
+// (The first step scales X0 by c >= SIGN_X_MAX: an eigenvalue delta starts at
+// x_0 = c delta, and |x_0| |1 - s| / 2 bounds its error.)
 SignPlan sign_plan(double tol, int n) {
   static std::mutex mu;
   static std::map<std::pair<double, int>, SignPlan> cache;
@@ -1580,20 +1579,24 @@ SignPlan sign_plan(double tol, int n) {
   for (int j = 0; j <= 256 * dec; ++j) d.push_back(std::pow(10.0, -dec + j / 256.0));
   for (int j = 1; j <= 1024; ++j) d.push_back(SIGN_X_MAX * j / 1024.0);
   const auto fast = [](double v) { return v * (3.0 - 3.2 * v * v + 1.2 * v * v * v * v); };
-  const auto newton = [](double v) { return v * (3.0 - v * v) / 2.0; };
-  // Newton-Schulz steps after which the starting points marked in `in` meet
-  // the bound from the iterates x (0 if not within `most`)
-  const auto steps = [&](std::vector<double> x, const std::vector<char> &in, int least, int most,
+  const auto finish = [](double v, int j) {
+    const SignStep p = sign_finish_step(j);
+    const double r = 1.0 - v * v;
+    return v * (p.b0 + r * (p.b1 + r * p.b2));
+  };
+  // finishing steps after which the starting points marked in `in` meet the
+  // bound from the iterates x (`most` if that takes more)
+  const auto steps = [&](std::vector<double> x, const std::vector<char> &in, int most,
                          double bound) {
-    for (int k2 = 1; k2 <= most; ++k2) {
+    for (int n2 = 1; n2 < most; ++n2) {
       double e = 0.0;
       for (size_t j = 0; j < d.size(); ++j) {
-        x[j] = newton(x[j]);
+        x[j] = finish(x[j], n2 - 1);
         if (in[j]) e = std::max(e, d[j] * std::fabs(1.0 - x[j]) / 2.0);
       }
-      if (k2 >= least && e <= bound) return k2;
+      if (e <= bound) return n2;
     }
-    return 0;
+    return most;
   };
   std::vector<double> x(d);
   std::vector<char> in(d.size());
@@ -1602,13 +1605,11 @@ SignPlan sign_plan(double tol, int n) {
     for (double &v : x) v = fast(v);
     if (k == 0 || k >= SignPlan::KMAX) continue;
     // (1.5e-16: what the double-precision iterates resolve)
-    const int n2 = steps(x, in, 1, 15, std::max(target / 4, std::min(target, 1.5e-16)));
-    if (n2 > 0 && 3 * (k + 1) + 2 * n2 < 3 * pl.k1 + 2 * pl.k2) pl.set_steps_after(k, n2);
+    pl.set_steps_after(k, steps(x, in, 15, std::max(target / 3, std::min(target, 1.5e-16))));
   }
   // the worst case from the scaled start (x_0 up to SIGN_X_MAX)
   std::fill(in.begin(), in.end(), 1);
-  const int n2 = steps(x, in, pl.k2, 12, target);
-  if (n2 > 0) pl.k2 = n2;
+  pl.k2 = steps(x, in, 12, target);
   cache.emplace(key, pl);
   return pl;
 }
@@ -1798,16 +1799,17 @@ __device__ __forceinline__ void sign_symmetrise(const T (&v)[TB * TB][4], T (&ds
 }
 
 // x <- sign(x) for x = W / ||W||_F of a block of s vertices (zero outside),
-// in at most pl.k1 fast and pl.k2 Newton-Schulz steps.  The squares Y = X^2
-// that every fast step forms tell how far the iteration is: once
-// ||I - Y||_F <= SIGN_THETA every eigenvalue is near +-1, and the Newton-Schulz
-// steps that remain are looked up (SignPlan).  The norm is formed beside the
-// two products that follow Y, so the test costs no latency; the step in
-// flight is finished.
+// in at most pl.k1 fast and pl.k2 finishing steps, all X <- X (b0 I + b1 R +
+// b2 R^2) with R = I - X^2 (near the end R is small, so the products' rounding
+// errors hardly reach X).  The residuals R tell how far the iteration is: once
+// ||R||_F <= SIGN_THETA every eigenvalue is near +-1, and the finishing steps
+// that remain are looked up (SignPlan).  The norm is formed beside the two
+// products that follow, so the test costs no latency; the step in flight is
+// finished.
 // Bound: the matrix cores (FP64: 64 cycles per 16x16x4 step), then the latency
 // of the chain of products, so their number is what counts.  On blocks with
-// independent N(0,1) entries it falls from 92 to about 25 (FP64, s = 16) and
-// from 41 to 22 (FP32).
+// independent N(0,1) entries it falls from 92 to about 23 (FP64, s = 16) and
+// from 41 to 20.5 (FP32); 24.4 and 22.4 with Newton-Schulz steps at the end.
 template <typename T, int TB>
 __device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const SignPlan &pl, T *C) {
   constexpr int NTL = TB * TB;
@@ -1823,41 +1825,36 @@ __device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const Si
   // one loop body for both kinds of step (a wave runs it for the first time
   // on every launch, and its instructions come from memory then: with a loop
   // each the projection of 2000 FP32 blocks of 16 took 13.4 us instead of 12.3)
-  int k = 0, k1 = pl.k1, n2 = pl.k2;   // fast steps done and allowed; steps left after them
-  T a1 = T(3), a3 = T(-3.2), a5 = T(1.2);
+  int k = 0, k1 = pl.k1, n2 = pl.k2, j = 0;   // fast steps done and allowed; finishing steps
+                                              // needed and done
   for (int it = 0;; ++it) {
     T y[NTL][4], m[NTL][4], z[NTL][4];
-    sign_prod<T, TB>(x, x, y);                                  // Y = X^2
-    bool last = false;
-    if (k < k1) {
-      const T one = k == 0 ? T(0) : T(1);
-      T d2 = T(0);
+    SignStep p = SIGN_FAST;
+    sign_prod<T, TB>(x, x, y);                                  // X^2
+    const bool first = it == 0 && k1 > 0;
+    const T one = first ? T(0) : T(1);
+    T d2 = T(0);
 #pragma unroll
-      for (int t = 0; t < NTL; ++t)
+    for (int t = 0; t < NTL; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const T d = one * id[t][r] - y[t][r];
-          d2 += d * d;
-        }
-      const float e2 = wave_total_f32((float)d2);
-      if (k == 0) {
-        const T c = (T)sign_scale(e2);
-        a1 *= c;
-        a3 *= c * c * c;
-        a5 *= c * c * c * c * c;
+      for (int r = 0; r < 4; ++r) {
+        y[t][r] = one * id[t][r] - y[t][r];                     // R (first step: -X^2)
+        d2 += y[t][r] * y[t][r];
       }
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = a3 * id[t][r] + a5 * y[t][r];
-      sign_prod<T, TB>(y, m, z);                                // Z = Y (-3.2 I + 1.2 Y)
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = a1 * id[t][r] + z[t][r];   // 3 I + Z
-      a1 = T(3);
-      a3 = T(-3.2);
-      a5 = T(1.2);
+    bool last = false;
+    T b0 = T(1), b1 = T(0), b2 = T(0);
+    if (k < k1) {
+      const float e2 = wave_total_f32((float)d2);
+      if (first) {   // the fast step of c X in powers of X
+        const T c = (T)sign_scale(e2);
+        b0 = T(SIGN_FAST_1) * c;
+        b1 = T(-SIGN_FAST_3) * (c * c * c);
+        b2 = T(SIGN_FAST_5) * (c * c * c * c * c);
+      } else {
+        b0 = T(p.b0);
+        b1 = T(p.b1);
+        b2 = T(p.b2);
+      }
       const int stop = pl.steps_after(k);   // (0 for k = 0)
       ++k;
       if (stop > 0 && e2 <= SIGN_THETA * SIGN_THETA) {
@@ -1865,13 +1862,22 @@ __device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const Si
         n2 = stop;
       }
     } else {
-#pragma unroll
-      for (int t = 0; t < NTL; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[t][r] = T(1.5) * id[t][r] - T(0.5) * y[t][r];
-      last = --n2 == 0;
+      p = sign_finish_step(j);
+      b0 = T(p.b0);
+      b1 = T(p.b1);
+      b2 = T(p.b2);
+      last = ++j == n2;
     }
-    sign_prod<T, TB>(x, m, z);   // X <- X (3 I + Z) or X (3 I - X^2) / 2
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m[t][r] = b1 * id[t][r] + b2 * y[t][r];
+    sign_prod<T, TB>(y, m, z);                                  // R (b1 I + b2 R)
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m[t][r] = b0 * id[t][r] + z[t][r];
+    sign_prod<T, TB>(x, m, z);
     if ((it & 1) || last) {
       sign_symmetrise<T, TB>(z, x, C);
     } else {
@@ -2263,12 +2269,12 @@ __device__ __forceinline__ void sb_pass(T *L, const T (&x)[N / 16][4], T alpha, 
 // matrix L in LDS and its right operand M from registers: the wave's column
 // block of M in the matrix cores' result layout (register r of lane l in row
 // block K holds M(16K + R(g, r), 16J + c), g = l / 16, c = l % 16), which is
-// exactly the right operand of step (K, r) of a product.  (Z = Y (-3.2 I +
-// 1.2 Y) reads both operands from LDS.)  The lower tiles of a result go to
+// exactly the right operand of step (K, r) of a product.  (R (b1 I + b2 R)
+// reads both operands from LDS.)  The lower tiles of a result go to
 // LDS on both sides of the diagonal, so every iterate is exactly symmetric,
 // and a wave reloads its column block of X from there after each step.  All
-// factors are polynomials in W and commute, so the fast step X (3 I + Z) is
-// formed as (3 I + Z) X with X the register operand, and the result as S W,
+// factors are polynomials in W and commute, so the step's X (b0 I + Z) is
+// formed as (b0 I + Z) X with X the register operand, and the result as S W,
 // which also goes to LDS for the epilogue.
 // MODE: 0 standalone (row-major s x s blocks in `in` / `out`), 1 Algorithm
 // 1's clique step (X_k, Lambda_k and the five residual partials, as
@@ -2445,72 +2451,73 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
     }
 #undef SDP_SB_PASS
   };
-  // The passes of the fast steps (L = X X; L = 3 I + L (-3.2 I + 1.2 L);
-  // L = L X, then x = L) and of the Newton-Schulz steps (L = 1.5 I -
-  // 0.5 X X; L = L X, then x = L), and a last one, L = S W with W again in
-  // x.  As in sign_iterate, the norm of I - X X that the first pass of a fast
-  // step leaves in LDS ends the fast steps early (the step is finished), and
-  // the first one is scaled.  (The lane index passes through an empty asm
-  // statement at each pass, so that the LDS addresses derived from it are
-  // formed in the pass instead of hoisted out of the loop and kept live,
-  // which spills.)
+  // The passes of a step (L = R = I - X X; L = b0 I + L (b1 I + b2 L);
+  // L = L X, then x = L), and a last one, L = S W with W again in x.  As in
+  // sign_iterate, the norm of R that the first pass of a fast step leaves in
+  // LDS ends the fast steps early (the step is finished), and the first one is
+  // scaled.  (The lane index passes through an empty asm statement at each
+  // pass, so that the LDS addresses derived from it are formed in the pass
+  // instead of hoisted out of the loop and kept live, which spills.)
   // Bound: a workgroup per clique, by the matrix cores of its one compute
   // unit (67% of their FP64 peak for N = 128), so the number of passes counts.
-  int k = 0, n2 = pl.k2;
-  int ph = __builtin_amdgcn_readfirstlane(f2 == 0.0) ? 4 : pl.k1 > 0 ? 0 : 3;
-  T c1 = T(1), c3 = T(1), c5 = T(1);
-  bool last_fast = false;
-  // ph: 0 Y, 1 Z, 2 X of a fast step; 3 Y, 5 X of a Newton-Schulz step; 4 S W
+  int k = 0, k1 = pl.k1, n2 = pl.k2, j = 0;   // as in sign_iterate
+  int ph = __builtin_amdgcn_readfirstlane(f2 == 0.0) ? 3 : 0;
+  T b0 = T(1), b1 = T(0), b2 = T(0);
+  bool last = false;
+  // ph: 0 R, 1 the polynomial of R, 2 X; 3 S W
   for (;;) {
     int lq = l;
     asm volatile("" : "+v"(lq));
     const int gq = lq >> 4, cq = lq & 15;
-    if (ph == 4) gather_w();
-    T sa = T(0), sb = T(1);
-    if (ph == 1) sa = T(3) * c1;
-    if (ph == 3) {
-      sa = T(1.5);
-      sb = T(-0.5);
-    }
+    if (ph == 3) gather_w();
+    const bool first = k == 0 && k1 > 0;
     if (ph == 1)
-      pass(std::true_type(), T(-3.2) * c3, T(1.2) * c5, sa, sb, gq, cq, nullptr, T(0));
+      pass(std::true_type(), b1, b2, b0, T(1), gq, cq, nullptr, T(0));
     else
-      pass(std::false_type(), T(0), T(0), sa, sb, gq, cq, ph == 0 ? fred : nullptr,
-           k == 0 ? T(0) : T(1));
-    if (ph == 4) break;
-    if (ph == 2 || ph == 5) {
+      pass(std::false_type(), T(0), T(0), ph == 0 && !first ? T(1) : T(0), ph == 0 ? T(-1) : T(1),
+           gq, cq, ph == 0 && k < k1 ? fred : nullptr, first ? T(0) : T(1));
+    if (ph == 3) break;
+    if (ph == 2) {
 #pragma unroll
       for (int K = 0; K < TN; ++K)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           x[K][r] = L[(16 * K + sign16_row<T>(gq, r)) * P + 16 * J + cq];
-    }
-    if (ph == 0) {
-      float e2 = k == 0 ? 0.0f : (float)s;
-#pragma unroll
-      for (int i = 0; i < NT / 64; ++i) e2 += fred[i];
-      c1 = k == 0 ? (T)sign_scale(e2) : T(1);
-      c3 = c1 * c1 * c1;
-      c5 = c3 * c1 * c1;
-      // (the same in every lane; the broadcast tells the compiler, which
-      // otherwise masks lanes off through the passes)
-      const int near1 = __builtin_amdgcn_readfirstlane(e2 <= SIGN_THETA * SIGN_THETA);
-      const int stop = pl.steps_after(k);   // (0 for k = 0)
-      ++k;
-      last_fast = k == pl.k1;
-      if (near1 && stop > 0) {
-        last_fast = true;
-        n2 = stop;
-      }
-      ph = 1;
+      ph = last ? 3 : 0;
     } else if (ph == 1) {
       ph = 2;
-    } else if (ph == 2) {
-      ph = !last_fast ? 0 : n2 > 0 ? 3 : 4;
-    } else if (ph == 3) {
-      ph = 5;
     } else {
-      ph = --n2 > 0 ? 3 : 4;
+      if (k < k1) {
+        float e2 = first ? 0.0f : (float)s;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) e2 += fred[i];
+        if (first) {   // the fast step of c X in powers of X
+          const T c = (T)sign_scale(e2);
+          b0 = T(SIGN_FAST_1) * c;
+          b1 = T(-SIGN_FAST_3) * (c * c * c);
+          b2 = T(SIGN_FAST_5) * (c * c * c * c * c);
+        } else {
+          b0 = T(SIGN_FAST.b0);
+          b1 = T(SIGN_FAST.b1);
+          b2 = T(SIGN_FAST.b2);
+        }
+        // (the same in every lane; the broadcast tells the compiler, which
+        // otherwise masks lanes off through the passes)
+        const int near1 = __builtin_amdgcn_readfirstlane(e2 <= SIGN_THETA * SIGN_THETA);
+        const int stop = pl.steps_after(k);   // (0 for k = 0)
+        ++k;
+        if (near1 && stop > 0) {
+          k1 = k;
+          n2 = stop;
+        }
+      } else {
+        const SignStep p = sign_finish_step(j);
+        b0 = T(p.b0);
+        b1 = T(p.b1);
+        b2 = T(p.b2);
+        last = ++j == n2;
+      }
+      ph = 1;
     }
   }
 

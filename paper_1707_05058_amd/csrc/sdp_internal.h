@@ -134,8 +134,8 @@ int projection_default_variant(int precision, int s);   // -1 if s is too large 
 // (tol, n); thread-safe)
 void sign_schedule(double tol, int n, int *k1, int *k2);
 // What the sign-function kernels run (sign_plan): at most k1 fast and k2
-// Newton-Schulz steps; and, for an iteration that has come near +-1 after k
-// fast steps, the Newton-Schulz steps left after one more fast step.
+// finishing steps; and, for an iteration that has come near +-1 after k fast
+// steps, the finishing steps left after one more fast step.
 constexpr float SIGN_THETA = 0.9f;    // ||I - X^2||_F that counts as near
 constexpr float SIGN_X_MAX = 1.25f;   // bound of the scaled start (the fast map's basin ends at 1.29)
 struct SignPlan {
@@ -149,6 +149,27 @@ struct SignPlan {
   }
   void set_steps_after(int k, int n) { (k < 16 ? lo : hi) |= (uint64_t)n << (4 * (k & 15)); }
 };
+// One step x <- x (b0 + b1 r + b2 r^2), r = 1 - x^2.
+struct SignStep {
+  double b0, b1, b2;
+};
+// The fast step 3 x - 3.2 x^3 + 1.2 x^5: eigenvalues near 0 grow threefold, and
+// [0, 1.25] stays in [0, 1.2105].
+constexpr double SIGN_FAST_1 = 3.0, SIGN_FAST_3 = -3.2, SIGN_FAST_5 = 1.2;
+constexpr SignStep SIGN_FAST = {SIGN_FAST_1 + SIGN_FAST_3 + SIGN_FAST_5,
+                                -SIGN_FAST_3 - 2.0 * SIGN_FAST_5, SIGN_FAST_5};
+// The finishing steps.  A fast step takes the eigenvalues that ||I - X^2||_F <=
+// 0.9 leaves, [0.316, 1.21], to [0.851, 1.2105]; step 0 is the best uniform
+// approximation of +1 there (within 0.0034), step 1 the third-order step for
+// that range (2.5 ((x - 1)^3 - 3/4 h^2 (x - 1)) about 1: within 2.5e-8), the
+// later ones the third-order step itself (15 x - 10 x^3 + 3 x^5) / 8.  Two of
+// them do for FP32 and three for FP64, 6 and 9 products, where Newton-Schulz
+// steps x (3 - x^2) / 2 took 8 and 10.
+__host__ __device__ inline SignStep sign_finish_step(int j) {
+  constexpr double H = 0.00338;
+  return j == 0 ? SignStep{1.002014, 0.523437, 0.325222}
+                : SignStep{1.0, j == 1 ? 0.5 + 0.9375 * H * H : 0.5, 0.375};
+}
 SignPlan sign_plan(double tol, int n);   // cached per (tol, n); thread-safe
 int projection_standalone_variant(int precision, int s);  // sign function where built
 hipError_t fill_random_blocks(int precision, void *out, int s, int count, uint32_t seed,
