@@ -160,9 +160,9 @@ def load_traffic(workload, stage):
 # kernels of each stage as rocprofv3 names them, (prefix, suffix) pairs; the
 # projection is the FP32-eig form's ADMM-mode kernel (template mode 0, or 3 with the
 # positive/negative decoupling compiled in)
-STAGE_KERNELS = {"scatter": (("k_scatter", ""),), "A_v": (("k_rowdot<", ""), ("k_csr_rowdot", "")),
+STAGE_KERNELS = {"scatter": (("k_scatter", ""),), "A_v": (("k_rowdot<", ""), ("k_fused<", ""), ("k_csr_rowdot", "")),
                  "Linv_r": (("k_trmv_wave<0>", ""),), "LinvT_y": (("k_trmv_wave<1>", ""),),
-                 "AT_y": (("k_coldot<0,", ""), ("k_csc_coldot<0>", "")),
+                 "AT_y": (("k_coldot<0,", ""), ("k_fused_reduce", ""), ("k_csc_coldot<0>", "")),
                  "projection": (("k_project<float", ", 0, false>"), ("k_project<float", ", 0, true>"),
                                 ("k_project<float", ", 3, false>"), ("k_admm_sign<float", "")),
                  "residual": (("k_residual_reduce", ""),)}

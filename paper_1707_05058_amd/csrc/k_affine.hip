@@ -1035,19 +1035,18 @@ hipError_t launch_objective(const AffineArgs &a, double *obj, hipStream_t st) {
 // The fused pass's tiles for the dense instances (m, ld) of a handle: empty
 // where it would not pay.  A cluster of G = ceil(ld / FU_COLS) workgroups
 // takes a group of rows; one workgroup runs per compute unit, so the groups
-// are as long as fills the chip once (256 workgroups), up to FU_GROUP rows,
-// past which the column sums (written and read once per group) are below 2%
-// of B.
+// are as long as fills the chip once (256 workgroups).
 FusedPlan plan_fused(const std::vector<InstDesc> &inst) {
-  constexpr int UNITS = 256, FU_GROUP = 128;
+  constexpr int UNITS = 256;
   FusedPlan p;
-  int64_t chunks = 0, bytes = 0;
+  int64_t chunks = 0, bytes = 0, most = 1;
   for (const InstDesc &d : inst) {
     if (d.a_format != 0 || d.m <= 0) continue;
     const int G = (d.ld + FU_COLS - 1) / FU_COLS;
     if (G > FU_MAXG) return FusedPlan();
     chunks += (int64_t)d.m * G;
     bytes += 8 * (int64_t)d.m * d.ld;
+    most = std::max<int64_t>(most, d.m);
   }
   if (bytes < FUSED_MIN_BYTES) return FusedPlan();
   const auto count = [&](int64_t rows) {
@@ -1056,9 +1055,14 @@ FusedPlan plan_fused(const std::vector<InstDesc> &inst) {
       if (d.a_format == 0) n += (d.m + rows - 1) / rows * ((d.ld + FU_COLS - 1) / FU_COLS);
     return n;
   };
+  // One workgroup per unit, so that the members of a cluster run at the same
+  // time: with more, they start when units fall free, and members waiting for
+  // one another (then computing the missing parts) took 44 ms for the 31.8 GB of
+  // 512 instances, against 9.4 in two passes.
   int64_t rows = std::max<int64_t>((chunks + UNITS - 1) / UNITS, 1);
-  while (rows <= FU_GROUP && count(rows) > UNITS) ++rows;
-  rows = std::min<int64_t>(rows, FU_GROUP);
+  while (rows < most && count(rows) > UNITS) ++rows;
+  // (with less than 60% of the units' rows in use, two passes are no slower)
+  if (count(rows) > UNITS || 10 * chunks < 6 * UNITS * rows) return FusedPlan();
   p.part_first.assign(2 * inst.size(), 0);
   for (size_t i = 0; i < inst.size(); ++i) {
     const InstDesc &d = inst[i];

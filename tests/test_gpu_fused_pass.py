@@ -71,12 +71,18 @@ def run(sdp, insts, n, stream=None):
         return [S.solution(i)["u"] for i in range(len(insts))]
 
 
-def test_more_clusters_than_units(sdp, gpu, oracle_mod):
-    """40 copies of one instance make more workgroups than there are units, so
-    some members of a cluster start late: every copy comes out the same, and
-    as the oracle has it."""
-    inst = members2()
-    us = run(sdp, [inst] * 40, 10)
+@pytest.mark.parametrize("copies", [4, 85, 128, 129])
+def test_many_instances(sdp, gpu, oracle_mod, copies):
+    """Copies of one instance of two members each: 4 and 85 (whose clusters
+    leave units idle) and 128 (a workgroup per unit) take the fused pass, 129
+    (more clusters than units, which would wait for members that have not
+    started) the two separate passes.  Every copy comes out the same, and as the
+    oracle has it."""
+    inst = sdpgen.block_arrow_instance(20, 16, 5, 41, seed=7)
+    assert 4096 < inst.nnz <= 8192
+    if copies == 4:
+        inst = members2()
+    us = run(sdp, [inst] * copies, 10)
     for u in us[1:]:
         assert rel_err(u, us[0]) <= 1e-12
     P = oracle_mod.Problem(inst)
