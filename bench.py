@@ -870,7 +870,9 @@ def sign_products(sdp, prec, N, threads):
     three products, k2 Newton-Schulz steps of two, one final product, at
     2 N 16^2 flops per 16 x 16 tile; the LDS kernels form the TN (TN + 1) / 2
     tiles on or below the diagonal, the one-wave register kernels for N = 32
-    all TN^2 (each off-diagonal tile is the other's operand)."""
+    all TN^2 (each off-diagonal tile is the other's operand).  That is the
+    schedule for the worst spectrum; the kernels stop once the iterate is near
+    (N(0,1) blocks: about half of it in FP32, a quarter to a third in FP64)."""
     tol = 1e-6 if prec == "fp32" else 1e-14
     k1, k2 = sdp.sign_schedule(tol, N)
     tn = N // 16
@@ -979,7 +981,7 @@ def run_projection(args, sdp, torch, stream):
                               "rebuild s^3)",
                      "executed": head["executed_matrix_tflops"],
                      "executed_frac": head["executed_frac_of_peak"],
-                     "executed_model": "sign method: (3 k1 + 2 k2 + 1) products of the padded "
+                     "executed_model": "sign method, at most: (3 k1 + 2 k2 + 1) products of the padded "
                                        "N x N block, 2 N 16^2 flops per 16 x 16 tile; the LDS "
                                        "kernels form the TN (TN + 1) / 2 tiles on or below the "
                                        "diagonal (TN = N / 16), the one-wave register kernel "
