@@ -1057,8 +1057,8 @@ FusedPlan plan_fused(const std::vector<InstDesc> &inst) {
   };
   // One workgroup per unit, so that the members of a cluster run at the same
   // time: with more, they start when units fall free, and members waiting for
-  // one another (then computing the missing parts) took 44 ms for the 31.8 GB of
-  // 512 instances, against 9.4 in two passes.
+  // one another (then computing the missing parts) took 50 ms for the 31.8 GB of
+  // 512 instances, against 9.5 in two passes.
   int64_t rows = std::max<int64_t>((chunks + UNITS - 1) / UNITS, 1);
   while (rows < most && count(rows) > UNITS) ++rows;
   // (with less than 60% of the units' rows in use, two passes are no slower)
