@@ -2908,7 +2908,8 @@ __global__ __launch_bounds__(SPLIT_GNT) void k_split_epilogue(ProjArgs a, const 
   }
 }
 
-// The launches of one split projection: gather, 3 k1 + 2 k2 + 1 products,
+// The launches of one split projection: gather, 3 k1 + 2 k2 + 1 products
+// (sign_schedule's counts: Newton-Schulz steps from the unscaled start),
 // epilogue.  ws holds 4 N^2 + SPLIT_META doubles per clique of the list.
 template <int N, int MODE>
 hipError_t launch_split(const ProjArgs &a, const int32_t *list, int count, double *ws, int k1,
@@ -2952,11 +2953,16 @@ hipError_t launch_sign(int count, const int32_t *sizes, const int64_t *offsets, 
 }
 
 hipError_t dispatch_sign(int dtype, int N, int NT, int count, const int32_t *sizes,
-                         const int64_t *offsets, const void *in, void *out, const SignPlan &pl,
+                         const int64_t *offsets, const void *in, void *out, double tol,
                          hipStream_t st) {
+  const SignPlan pl = sign_plan(tol, N);
+  // (Newton-Schulz steps from the unscaled start: the schedule's own counts)
 #define SDP_SIGN(T, n, nt)                                                                     \
-  if (N == n && NT == nt)                                                                      \
-    return launch_sign<T, n, nt>(count, sizes, offsets, in, out, pl.k1, pl.k2, st);
+  if (N == n && NT == nt) {                                                                    \
+    int k1, k2;                                                                                \
+    sign_schedule(tol, N, &k1, &k2);                                                           \
+    return launch_sign<T, n, nt>(count, sizes, offsets, in, out, k1, k2, st);                  \
+  }
   // blocks of 16 and 32: the register-resident kernels
 #define SDP_SIGN_REGS(T, n)                                                                    \
   if (N == n && NT == 64) {                                                                    \
@@ -3088,11 +3094,13 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
       const SignPlan pl = sign_plan(a.tol, N);
       if (split_ws && split_workspace(precision, variant, count) > 0) {
         const int mode = a.hsde ? 3 : a.dual ? 2 : 1;
+        int k1, k2;   // of Newton-Schulz steps, not the plan's finishing steps
+        sign_schedule(a.tol, N, &k1, &k2);
 #define SDP_SPLIT(n)                                                                           \
   if (N == n) {                                                                                \
-    if (mode == 3) return launch_split<n, 3>(a, list, count, split_ws, pl.k1, pl.k2, st);      \
-    if (mode == 2) return launch_split<n, 2>(a, list, count, split_ws, pl.k1, pl.k2, st);      \
-    return launch_split<n, 1>(a, list, count, split_ws, pl.k1, pl.k2, st);                     \
+    if (mode == 3) return launch_split<n, 3>(a, list, count, split_ws, k1, k2, st);            \
+    if (mode == 2) return launch_split<n, 2>(a, list, count, split_ws, k1, k2, st);            \
+    return launch_split<n, 1>(a, list, count, split_ws, k1, k2, st);                           \
   }
         SDP_SPLIT(96)
         SDP_SPLIT(128)
@@ -3135,7 +3143,7 @@ hipError_t launch_standalone_projection(int dtype, int variant, int count, const
   projection_variant_info(dtype, variant, &N, &NT);
   if (projection_variant_kind(dtype, variant) == 2) {
     if (count <= 0) return hipSuccess;
-    return dispatch_sign(dtype, N, NT, count, sizes, offsets, in, out, sign_plan(tol, N), st);
+    return dispatch_sign(dtype, N, NT, count, sizes, offsets, in, out, tol, st);
   }
   const int blk = projection_variant_two_level(dtype, variant);
   if (dtype == 1)
