@@ -1743,11 +1743,10 @@ __device__ inline float wave_total_f32(float v) {
   v += ror(v, std::integral_constant<int, 0x124>());   // row_ror:4
   v += ror(v, std::integral_constant<int, 0x122>());   // row_ror:2
   v += ror(v, std::integral_constant<int, 0x121>());   // row_ror:1
-  const int b = __float_as_int(v);
-  return (__int_as_float(__builtin_amdgcn_readlane(b, 0)) +
-          __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
-         (__int_as_float(__builtin_amdgcn_readlane(b, 32)) +
-          __int_as_float(__builtin_amdgcn_readlane(b, 48)));
+  // rows 1 and 3 add the row before, row 3 adds row 1: the total in lane 63
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xc, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // The scale of the first fast step: ||X^2||_F^(1/2) bounds the largest
@@ -1890,6 +1889,96 @@ __device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const Si
   }
 }
 
+// The same with as few instructions as a step can do with, for launches of few
+// FP32 cliques of 16: sign_schedule's k1 fast and k2 Newton-Schulz steps from the
+// unscaled start, unless ||I - X^2||_F <= SIGN_THETA is seen in one of the odd
+// steps, which wait for LDS anyway.  A wave alone on its SIMD pays the latency
+// of every instruction, and the first run of each line of code in a launch
+// comes from memory; the iterates of a settled solve often have eigenvalues at
+// 0 and take every step.  FP32, us per iteration, sign_iterate -> this, the
+// first 50 / after 700 iterations: 118 cliques of 10 23.4 / 24.7 -> 22.9 / 23.8,
+// 10 of 15 17.5 / 17.7 -> 17.6 / 17.4, 4096 of 16 43.1 / 46.9 -> 42.8 / 45.5.
+// Where launches fill the chip, and for blocks of 32, the steps that stopping
+// sooner saves count for more: 20000 of 16 123 / 142 -> 125 / 139, 50 of 24
+// 45.0 / 44.2 -> 46.3 / 45.5.
+template <typename T, int TB>
+__device__ __forceinline__ void sign_iterate_few(T (&x)[TB * TB][4], int s, const SignPlan &pl,
+                                                 T *C) {
+  constexpr int NTL = TB * TB;
+  const int g = threadIdx.x >> 4, col = threadIdx.x & 15;
+  T id[NTL][4];   // the identity on the block's own vertices
+#pragma unroll
+  for (int t = 0; t < NTL; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * (t / TB) + sign16_row<T>(g, r);
+      id[t][r] = (t % (TB + 1) == 0 && row == 16 * (t % TB) + col && row < s) ? T(1) : T(0);
+    }
+  const int k1 = pl.k1, n = pl.k1 + pl.k2;
+  int stop = 0;   // fitted finishing steps once near +-1
+#pragma unroll 1
+  for (int it = 0; it < n; ++it) {
+    T y[NTL][4], m[NTL][4], z[NTL][4];
+    sign_prod<T, TB>(x, x, y);                                  // Y = X^2
+    if (it < k1) {
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[t][r] = T(SIGN_FAST_3) * id[t][r] + T(SIGN_FAST_5) * y[t][r];
+      sign_prod<T, TB>(y, m, z);                                // Y (-3.2 I + 1.2 Y)
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[t][r] = T(SIGN_FAST_1) * id[t][r] + z[t][r];
+    } else {
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[t][r] = T(1.5) * id[t][r] - T(0.5) * y[t][r];
+    }
+    sign_prod<T, TB>(x, m, z);
+    if ((it & 1) || it == n - 1) {
+      T d2 = T(0);
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d2 += (id[t][r] - y[t][r]) * (id[t][r] - y[t][r]);
+      const float e2 = wave_total_f32((float)d2);
+      sign_symmetrise<T, TB>(z, x, C);
+      if (__builtin_expect(e2 <= SIGN_THETA * SIGN_THETA && it < k1, 0)) {
+        stop = pl.steps_after(it);
+        if (stop > 0) break;
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[t][r] = z[t][r];
+    }
+  }
+#pragma unroll 1
+  for (int j = 0; j < stop; ++j) {
+    T y[NTL][4], m[NTL][4], z[NTL][4];
+    const SignStep p = sign_finish_step(j);
+    const T b0 = T(p.b0), b1 = T(p.b1), b2 = T(p.b2);
+    sign_prod<T, TB>(x, x, y);
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        y[t][r] = id[t][r] - y[t][r];
+        m[t][r] = b1 * id[t][r] + b2 * y[t][r];
+      }
+    sign_prod<T, TB>(y, m, z);
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m[t][r] = b0 * id[t][r] + z[t][r];
+    sign_prod<T, TB>(x, m, z);
+    sign_symmetrise<T, TB>(z, x, C);
+  }
+}
+
 // Standalone projections of row-major blocks of up to 16 TB vertices.
 template <typename T, int TB>
 __global__ __launch_bounds__(64) void k_project_sign_regs(const int32_t *__restrict__ sizes,
@@ -1964,7 +2053,7 @@ __global__ __launch_bounds__(64) void k_project_sign_regs(const int32_t *__restr
 // holds rows 16 I + R(g, r) at column 16 J + l mod 16.  W_k(i, k) and
 // W_k(k, i) come from the same packed entry, so W_k is exactly symmetric.
 // ---------------------------------------------------------------------------
-template <typename T, int TB, bool DUAL, bool HSDE = false>
+template <typename T, int TB, bool DUAL, bool HSDE, bool FEW>
 __global__ __launch_bounds__(64) void k_admm_sign(ProjArgs a, const int32_t *__restrict__ list,
                                                   SignPlan pl) {
   static_assert(!(DUAL && HSDE), "one algorithm per kernel");
@@ -2045,7 +2134,10 @@ __global__ __launch_bounds__(64) void k_admm_sign(ProjArgs a, const int32_t *__r
   for (int t = 0; t < NTL; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) x[t][r] = w[t][r] * scale;
-  if (f2 != 0.0) sign_iterate<T, TB>(x, s, pl, C);   // (uniform)
+  if (f2 != 0.0) {   // (uniform)
+    if constexpr (FEW) sign_iterate_few<T, TB>(x, s, pl, C);
+    else sign_iterate<T, TB>(x, s, pl, C);
+  }
   // X_k = P+(W) = (W + (W S + S W) / 2) / 2
   T c[NTL][4], cs[NTL][4];
   sign_prod<T, TB>(w, x, c);
@@ -3050,6 +3142,34 @@ hipError_t launch_sign_big(int N, const int32_t *list, int count, const ProjArgs
   return hipErrorInvalidValue;
 }
 
+// FP32 launches of up to this many cliques of 16 take sign_iterate_few: four
+// waves per SIMD (times there).
+constexpr int SIGN_FEW_16 = 4096;
+
+// The one-wave sign kernels on a list of cliques, in the mode of the algorithm.
+template <typename T, int TB>
+hipError_t launch_admm_sign(const int32_t *list, int count, const ProjArgs &a, hipStream_t st) {
+  SignPlan pl = sign_plan(a.tol, 16 * TB);
+  const auto launch = [&](auto few) {
+    constexpr bool F = decltype(few)::value;
+    const dim3 g(count), b(64);
+    if (a.hsde)
+      hipLaunchKernelGGL((k_admm_sign<T, TB, false, true, F>), g, b, 0, st, a, list, pl);
+    else if (a.dual)
+      hipLaunchKernelGGL((k_admm_sign<T, TB, true, false, F>), g, b, 0, st, a, list, pl);
+    else
+      hipLaunchKernelGGL((k_admm_sign<T, TB, false, false, F>), g, b, 0, st, a, list, pl);
+    return hipGetLastError();
+  };
+  if constexpr (sizeof(T) == 4 && TB == 1) {
+    if (count <= SIGN_FEW_16) {
+      sign_schedule(a.tol, 16 * TB, &pl.k1, &pl.k2);   // of Newton-Schulz steps
+      return launch(std::true_type());
+    }
+  }
+  return launch(std::false_type());
+}
+
 hipError_t launch_admm_projection(int precision, int variant, const int32_t *list, int count,
                                   const ProjArgs &a, hipStream_t st, double *split_ws) {
   int N, NT;
@@ -3061,30 +3181,11 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
     // V, theta) gets the Jacobi default of the same block size
     if (!a.eig && NT == 64 && (N == 16 || N == 32)) {
       if (count <= 0) return hipSuccess;
-      const SignPlan pl = sign_plan(a.tol, N);
-#define SDP_ADMM_SIGN(T, tb)                                                                    \
-  if (a.hsde)                                                                                   \
-    hipLaunchKernelGGL((k_admm_sign<T, tb, false, true>), dim3(count), dim3(64), 0, st, a, list, \
-                       pl);                                                                     \
-  else if (a.dual)                                                                              \
-    hipLaunchKernelGGL((k_admm_sign<T, tb, true>), dim3(count), dim3(64), 0, st, a, list, pl);   \
-  else                                                                                          \
-    hipLaunchKernelGGL((k_admm_sign<T, tb, false>), dim3(count), dim3(64), 0, st, a, list, pl);
-      if (precision == 1) {
-        if (N == 16) {
-          SDP_ADMM_SIGN(float, 1)
-        } else {
-          SDP_ADMM_SIGN(float, 2)
-        }
-      } else {
-        if (N == 16) {
-          SDP_ADMM_SIGN(double, 1)
-        } else {
-          SDP_ADMM_SIGN(double, 2)
-        }
-      }
-#undef SDP_ADMM_SIGN
-      return hipGetLastError();
+      if (precision == 1)
+        return N == 16 ? launch_admm_sign<float, 1>(list, count, a, st)
+                       : launch_admm_sign<float, 2>(list, count, a, st);
+      return N == 16 ? launch_admm_sign<double, 1>(list, count, a, st)
+                     : launch_admm_sign<double, 2>(list, count, a, st);
     }
     // larger cliques: one block in LDS, the other operand in registers (FP64
     // cliques of 97-128 have no variant with eigenvectors: the plan refuses
