@@ -224,6 +224,11 @@ __global__ __launch_bounds__(256) void k_hsde_reset(HsdeArgs h) {
 //                          3 ||(A^T u_y + H^T v_z)/tau - c||_W^2
 //   row-wave slots:        0 b^T g, 1 b^T u_y, 2 ||A W u_x||^2, 3 ||A W u_x - tau b||^2
 constexpr int WSLOT = 4;
+// Most wave partials of an instance that every wave of it sums itself: all
+// waves together read them quadratically often.  Banded FP64, us per iteration,
+// every wave -> a launch: 359 partials 62.7 -> 62.4, 712 79.8 -> 76.6, 5012 264 ->
+// 230, 15 640 836 -> 727.
+constexpr int64_t HSDE_WAVE_SUMS = 256;
 
 __global__ __launch_bounds__(256) void k_hsde_zs_partials(HsdeArgs h) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -251,11 +256,36 @@ __device__ inline double hsde_f(const HsdeArgs &h, int inst) {
   return h.hs[inst].kz * wsum(zs);
 }
 
-// f and tau = max(0, u_hat_tau - kappa) with u_hat_tau = omega_2 + f, in every
-// wave (a launch of its own for these scalars took 4.5 us; kappa and omega_2,
-// which the waves still read here, are updated by k_hsde_finish); u_x =
-// sigma_x - f mz_x, u_y = -g - f mz_y, A W u_x = nu_y + g - f A W mz_x, with
-// their wave partial sums.
+// tau = max(0, u_hat_tau - kappa) with u_hat_tau = omega_2 + f.
+__device__ inline double hsde_tau(const HsdeState &s, double f) {
+  const double uhat_tau = s.w2 + f;
+  return uhat_tau - s.kappa > 0.0 ? uhat_tau - s.kappa : 0.0;
+}
+
+// f and tau by one workgroup per instance, for instances of many partials.
+__global__ __launch_bounds__(HS_NT) void k_hsde_scalars(HsdeArgs h) {
+  __shared__ double red[HS_NT / 64];
+  const int inst = blockIdx.x;
+  if (h.state[inst].done) return;   // uniform per workgroup
+  const InstDesc d = h.inst[inst];
+  double zs = 0.0;
+  for (int64_t q = (d.coord_off >> 6) + threadIdx.x; q < (d.coord_off + d.ld) >> 6; q += HS_NT)
+    zs += h.cw_part[q * WSLOT];
+  for (int64_t q = (d.row_off >> 6) + threadIdx.x; q < (d.row_off + d.ldm) >> 6; q += HS_NT)
+    zs += h.rw_part[q * WSLOT];
+  zs = block_total<HS_NT>(zs, red);
+  if (threadIdx.x != 0) return;
+  HsdeState &s = h.hs[inst];
+  s.f = s.kz * zs;
+  s.tau = hsde_tau(s, s.f);
+}
+
+// u_x = sigma_x - f mz_x, u_y = -g - f mz_y, A W u_x = nu_y + g - f A W mz_x,
+// with their wave partial sums.  f and tau come from k_hsde_scalars (SUMMED),
+// or every wave forms them itself, which spares that launch (4.5 us) but reads
+// all of the instance's partials once per wave (HSDE_WAVE_SUMS).  (kappa and
+// omega_2, which the waves still read here, are updated by k_hsde_finish.)
+template <bool SUMMED>
 __global__ __launch_bounds__(256) void k_hsde_apply(HsdeArgs h) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int lane = threadIdx.x & 63;
@@ -263,12 +293,11 @@ __global__ __launch_bounds__(256) void k_hsde_apply(HsdeArgs h) {
     const int inst = h.coord_inst[t];
     double ctx = 0.0;
     if (!h.state[inst].done) {
-      const double f = hsde_f(h, inst);
       HsdeState &s = h.hs[inst];
-      if (t == h.inst[inst].coord_off) {
-        const double uhat_tau = s.w2 + f;
+      const double f = SUMMED ? s.f : hsde_f(h, inst);
+      if (!SUMMED && t == h.inst[inst].coord_off) {
         s.f = f;
-        s.tau = uhat_tau - s.kappa > 0.0 ? uhat_tau - s.kappa : 0.0;
+        s.tau = hsde_tau(s, f);
       }
       const double ux = h.sx[t] - f * h.mzx[t];
       h.ux[t] = ux;
@@ -281,10 +310,9 @@ __global__ __launch_bounds__(256) void k_hsde_apply(HsdeArgs h) {
     const int inst = h.row_inst[t];
     double bty = 0.0, ax2 = 0.0, rp2 = 0.0;
     if (!h.state[inst].done) {
-      const double f = hsde_f(h, inst);
       const HsdeState &s = h.hs[inst];
-      const double uhat_tau = s.w2 + f;
-      const double tau = uhat_tau - s.kappa > 0.0 ? uhat_tau - s.kappa : 0.0;
+      const double f = SUMMED ? s.f : hsde_f(h, inst);
+      const double tau = hsde_tau(s, f);
       const double uy = -h.g[t] - f * h.mzy[t];
       h.uy[t] = uy;
       bty = h.b[t] * uy;
@@ -483,7 +511,12 @@ hipError_t launch_hsde_update(const HsdeArgs &h, hipStream_t st) {
   const int64_t n = h.ncoord > h.nrow ? h.ncoord : h.nrow;
   const unsigned nb = (unsigned)((n + 255) / 256);
   hipLaunchKernelGGL(k_hsde_zs_partials, dim3(nb), dim3(256), 0, st, h);
-  hipLaunchKernelGGL(k_hsde_apply, dim3(nb), dim3(256), 0, st, h);
+  if (h.max_parts > HSDE_WAVE_SUMS) {
+    hipLaunchKernelGGL(k_hsde_scalars, dim3(h.batch), dim3(HS_NT), 0, st, h);
+    hipLaunchKernelGGL(k_hsde_apply<true>, dim3(nb), dim3(256), 0, st, h);
+  } else {
+    hipLaunchKernelGGL(k_hsde_apply<false>, dim3(nb), dim3(256), 0, st, h);
+  }
   return hipGetLastError();
 }
 

@@ -547,6 +547,8 @@ void setup_hsde(sdp_handle *h, const std::vector<double> &D) {
   g.mzt = dev_zeros<double>(pk, own);
   g.cw_part = dev_zeros<double>((size_t)(h->ncoord / 64 + 1) * 4, own);
   g.rw_part = dev_zeros<double>((size_t)(h->nrow / 64 + 1) * 4, own);
+  for (const InstDesc &d : h->desc)
+    g.max_parts = std::max<int64_t>(g.max_parts, (d.ld + d.ldm) / 64);
   g.part = p.part;
   g.inst_cl_first = a.inst_cl_first;
   g.hist = a.hist;

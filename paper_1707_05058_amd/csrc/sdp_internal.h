@@ -377,6 +377,7 @@ struct HsdeArgs {
   // wave partial sums (4 per 64 coordinates / rows), clique partials
   // (NPART per clique) and history
   double *cw_part, *rw_part;
+  int64_t max_parts;                  // wave partials of the largest instance
   const double *part;
   const int64_t *inst_cl_first;
   double *hist;
