@@ -736,8 +736,12 @@ void destroy_handle(sdp_handle *h) {
   delete h;
 }
 
+// one_pass: on entry whether the fused pass over B may be planned, on return
+// whether it was (also after a failure).
 void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_in,
-                sdp_handle **out) {
+                sdp_handle **out, bool &one_pass) {
+  const bool may_fuse = one_pass;
+  one_pass = false;
   if (!out) fail(SDP_ERR_ARG, "out is NULL");
   *out = nullptr;
   if (batch <= 0 || !inst) fail(SDP_ERR_ARG, "batch must be positive");
@@ -1080,7 +1084,8 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     h->d_t_rows_all = dev_upload(t_rows_all, own);
     h->n_t_rows_all = (int)(t_rows_all.size() / 2);
     h->d_ytmp = dev_zeros<double>(row, own);
-    const FusedPlan fp = d_A && !cg ? plan_fused(h->desc) : FusedPlan();
+    const FusedPlan fp = d_A && !cg && may_fuse ? plan_fused(h->desc) : FusedPlan();
+    one_pass = !fp.tiles.empty();
     if (opt.algorithm == SDP_ALG_HSDE) {
       // the embedding needs g = L^-T y1 itself on every row; its right-hand
       // side changes every iteration on both sides of the factor, so L^-1
@@ -1415,7 +1420,17 @@ void sdp_default_options(sdp_options *opt) {
 
 int sdp_setup(int32_t batch, const sdp_instance *inst, const sdp_options *opt, sdp_handle **out) {
   return guarded([&] {
-    setup_impl(batch, inst, opt, out);
+    bool one_pass = true;
+    try {
+      setup_impl(batch, inst, opt, out, one_pass);
+    } catch (SdpError &e) {
+      // the fused pass needs room for its partial sums, and in Algorithm 3 for
+      // B beside A: without it the handle may still fit
+      if (e.code != SDP_ERR_OOM || !one_pass) throw;
+      (void)hipGetLastError();
+      one_pass = false;
+      setup_impl(batch, inst, opt, out, one_pass);
+    }
     return SDP_OK;
   });
 }
