@@ -369,8 +369,19 @@ int sdp_time_stages(sdp_handle *h, int32_t n_iter, double *ms);
  * layout above; either may be NULL).  The factor does not depend on them. */
 int sdp_update_data(sdp_handle *h, const double *c, const double *b);
 
-/* Runs the T unrolled iterations from the initial state, keeping X_k and
- * Lambda_k every ckpt_every iterations for the reverse sweep, and copies u_T
+/* How much of the forward sdp_unrolled_forward keeps for the reverse sweep:
+ * every iteration's eigenvectors (FP32 in the SDP_FP32_EIG form) where those of
+ * all T iterations fit in max_bytes and on the device, else X_k and Lambda_k
+ * every ckpt_every iterations, from which sdp_vjp recomputes one segment at a
+ * time.  The results are the same.  Default 4 GiB; 0: checkpoints only, so that
+ * ckpt_every bounds the memory (the records of ckpt_every iterations and
+ * T / ckpt_every checkpoints).  Frees records beyond max_bytes (call the forward again before
+ * sdp_vjp then).  SDP_ERR_ARG if max_bytes < 0. */
+int sdp_set_unrolled_records(sdp_handle *h, int64_t max_bytes);
+
+/* Runs the T unrolled iterations from the initial state, keeping the
+ * eigenvectors of every iteration or X_k and Lambda_k every ckpt_every
+ * iterations (sdp_set_unrolled_records) for the reverse sweep, and copies u_T
  * to u_out (DEVICE, concatenated layout; may be NULL).  Needs adaptive_rho = 0,
  * SDP_ALG_PRIMAL, the cached factor and cliques of up to 128 vertices in
  * SDP_FP32_EIG or 96 in SDP_FP64 (SDP_ERR_UNSUPPORTED otherwise).
@@ -382,10 +393,9 @@ int sdp_unrolled_forward(sdp_handle *h, int32_t T, int32_t ckpt_every, double *u
  * layout).  With euclidean = 0 the cotangents of u and c are taken w.r.t. the
  * Frobenius inner product of the symmetric matrices (off-diagonal coordinates
  * weighted by 2); with euclidean = 1 w.r.t. the plain dot product of the
- * compact vectors (what an autodiff framework uses).  The forward keeps each
- * projection's eigenvectors (FP32 in the SDP_FP32_EIG form) where all of them
- * fit in 4 GiB; otherwise the segments between checkpoints are recomputed
- * forward, storing them, then reversed.  The projection adjoints run
+ * compact vectors (what an autodiff framework uses).  Where the forward kept
+ * checkpoints only, the segments between them are recomputed forward, storing
+ * each projection's eigenvectors, then reversed.  The projection adjoints run
  * on the matrix cores for cliques of up to 128 vertices in FP32 and 96 in
  * FP64 (larger ones: sdp_unrolled_forward returns SDP_ERR_UNSUPPORTED).  The
  * handle's iterate is unspecified afterwards (call

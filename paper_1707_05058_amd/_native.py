@@ -76,7 +76,7 @@ EXPORTS = ["sdp_default_options", "sdp_setup", "sdp_reset", "sdp_admm_step", "sd
            "sdp_get_solution", "sdp_set_state", "sdp_get_history",
            "sdp_diagnostics", "sdp_diagnostics_noalloc", "sdp_get_stats",
            "sdp_get_projection_stats", "sdp_projection_plan", "sdp_time_stages",
-           "sdp_update_data", "sdp_unrolled_forward", "sdp_vjp", "sdp_cg_steps", "sdp_destroy",
+           "sdp_update_data", "sdp_set_unrolled_records", "sdp_unrolled_forward", "sdp_vjp", "sdp_cg_steps", "sdp_destroy",
            "sdp_projection_variant_kind", "sdp_projection_plan_variants",
            "sdp_projection_default_variant", "sdp_sign_schedule",
            "sdp_last_error",
@@ -115,6 +115,7 @@ def _load():
     lib.sdp_projection_plan.argtypes = [_p, C.c_int32, ip, ip, ip, ip]
     lib.sdp_time_stages.argtypes = [_p, C.c_int32, dp]
     lib.sdp_update_data.argtypes = [_p, _p, _p]
+    lib.sdp_set_unrolled_records.argtypes = [_p, C.c_int64]
     lib.sdp_unrolled_forward.argtypes = [_p, C.c_int32, C.c_int32, _p]
     lib.sdp_vjp.argtypes = [_p, _p, _p, _p, C.c_int32]
     lib.sdp_cg_steps.argtypes = [_p, C.POINTER(C.c_int64)]
@@ -317,6 +318,11 @@ class Solver:
                 _check_tensor(t, n)
         _check(lib.sdp_update_data(self._h, None if c is None else C.c_void_p(c.data_ptr()),
                                    None if b is None else C.c_void_p(b.data_ptr())))
+
+    def set_unrolled_records(self, max_bytes: int):
+        """Most bytes of eigenvectors the unrolled forward keeps for vjp (default
+        4 GiB; 0: checkpoints every ckpt_every iterations only)."""
+        _check(lib.sdp_set_unrolled_records(self._h, int(max_bytes)))
 
     def unrolled_forward(self, T: int, ckpt_every: int, u_out=None):
         if u_out is not None:

@@ -1,7 +1,9 @@
 """torch.autograd.Function over the unrolled iteration (C, b) -> u_T.
 
 forward runs T iterations of Algorithm 1 (fixed rho, from X_k = Lambda_k = 0)
-through sdp_unrolled_forward with checkpoints every `ckpt_every` iterations;
+through sdp_unrolled_forward, which keeps the eigenvectors of every iteration
+or, where they do not fit (Solver.set_unrolled_records), checkpoints every
+`ckpt_every` iterations;
 backward calls sdp_vjp, the hand-written reverse sweep.  Tensors use the
 concatenated compact layout of the batch (c and u: lower pattern values of
 every instance one after the other; b: the m_i right-hand sides).  Gradients

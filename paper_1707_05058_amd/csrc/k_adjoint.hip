@@ -13,8 +13,8 @@
 //   affine stages: one KKT solve with b = 0: bhb = P ubar, ybar = multiplier
 //   k_adj_coord_gather:  cbar -= bhb / rho;  bbar += ybar;
 //                  Xb = H_k bhb;  Lb += H_k bhb / rho
-// The eigenvectors and eigenvalues of each W_k come from a recomputation of
-// the segment since the last checkpoint (k_project stores them).
+// The eigenvectors and eigenvalues of each W_k were stored by k_project in the
+// forward, or in a recomputation of the segment since the last checkpoint.
 #include "sdp_internal.h"
 #include "mfma_tile.h"
 

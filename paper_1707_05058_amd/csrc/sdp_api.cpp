@@ -243,6 +243,12 @@ int tune_variant(int precision, int s, int64_t count, int max_sweeps, double tol
 
 }  // namespace
 
+// The unrolled forward keeps every iteration's eigenvectors up to this many
+// bytes by default (1.5% of the card), which spares the reverse sweep the
+// recomputation of the segments; beyond it (sdp_set_unrolled_records),
+// checkpoints every ckpt_every iterations.
+constexpr int64_t EIG_ALL_BYTES = int64_t(4) << 30;
+
 struct sdp_handle {
   int B = 0;
   sdp_options opt{};
@@ -320,6 +326,7 @@ struct sdp_handle {
   int64_t ckpt_cap = 0;
   void *d_eigbuf = nullptr;              // (V, theta) records: [ckpt][eig_total], or [T] (eig_all)
   int64_t eigbuf_cap = 0;
+  int64_t eig_all_bytes = EIG_ALL_BYTES; // most bytes of records that a forward keeps
   bool eig_all = false;                  // the last forward kept every iteration's records
   double *d_Xb = nullptr, *d_Lb = nullptr, *d_Ub = nullptr;
   double *d_bhat_bar = nullptr, *d_v_bar = nullptr, *d_bhb = nullptr;
@@ -457,11 +464,6 @@ bool reserve_eigbuf(sdp_handle *h, int64_t records, bool may_fail) {
   h->eigbuf_cap = need;
   return true;
 }
-
-// The forward keeps every iteration's eigenvectors up to this many bytes (1.5%
-// of the card), which spares the reverse sweep the recomputation of the
-// segments; beyond it, checkpoints every ckpt_every iterations.
-constexpr int64_t EIG_ALL_BYTES = int64_t(4) << 30;
 
 // y = L^-T y1 for every row (with B = L^-1 A formed, the iteration keeps only y1).
 void ensure_y(sdp_handle *h) {
@@ -1890,6 +1892,23 @@ int sdp_update_data(sdp_handle *h, const double *c, const double *b) {
   });
 }
 
+int sdp_set_unrolled_records(sdp_handle *h, int64_t max_bytes) {
+  return guarded([&] {
+    if (!h || max_bytes < 0) fail(SDP_ERR_ARG, "invalid arguments");
+    h->eig_all_bytes = max_bytes;
+    const size_t esz = h->precision == SDP_FP32_EIG ? sizeof(float) : sizeof(double);
+    if ((double)esz * h->eigbuf_cap > (double)max_bytes && h->d_eigbuf) {
+      // (the last forward's records go with it)
+      HIPCHK(hipStreamSynchronize(h->stream));
+      (void)hipFree(h->d_eigbuf);
+      h->d_eigbuf = nullptr;
+      h->eigbuf_cap = 0;
+      if (h->eig_all) h->adj_T = 0;
+    }
+    return SDP_OK;
+  });
+}
+
 int sdp_unrolled_forward(sdp_handle *h, int32_t T, int32_t ckpt_every, double *u_out) {
   return guarded([&] {
     if (!h || T <= 0 || ckpt_every <= 0) fail(SDP_ERR_ARG, "invalid arguments");
@@ -1903,7 +1922,7 @@ int sdp_unrolled_forward(sdp_handle *h, int32_t T, int32_t ckpt_every, double *u
                                 "FP32 and 96 in FP64");
     const size_t esz = h->precision == SDP_FP32_EIG ? sizeof(float) : sizeof(double);
     h->adj_T = 0;
-    h->eig_all = (double)esz * h->eig_total * T <= (double)EIG_ALL_BYTES &&
+    h->eig_all = (double)esz * h->eig_total * T <= (double)h->eig_all_bytes &&
                  reserve_eigbuf(h, T, true);
     const int nseg = (T + ckpt_every - 1) / ckpt_every;
     const int64_t need = h->eig_all ? 0 : (int64_t)nseg * 2 * std::max<int64_t>(h->npk, 1);

@@ -3,6 +3,7 @@ Algorithm 3 then iterates with A and both triangular passes, as it does for
 small matrices.  The rest of the device is held by a tensor meanwhile, so an
 allocation fails as it would beside another program.  Bar: 1e-8 relative to
 the largest entry, as against the oracle, between the two forms."""
+import contextlib
 import gc
 
 import numpy as np
@@ -14,6 +15,28 @@ from test_gpu_admm import rel_err
 pytestmark = pytest.mark.gpu
 
 STEPS = 30
+
+
+@contextlib.contextmanager
+def fill_device(room):
+    """Everything on the device held by tensors but about `room` bytes."""
+    import torch
+    chunk = 64 << 20
+    torch.cuda.empty_cache()
+    hogs = [torch.empty(torch.cuda.mem_get_info()[0] - (4 << 30), dtype=torch.uint8, device="cuda")]
+    try:
+        for _ in range(512):                       # (the device holds more than it reports free)
+            try:
+                hogs.append(torch.empty(chunk, dtype=torch.uint8, device="cuda"))
+            except torch.cuda.OutOfMemoryError:
+                break
+        del hogs[1:1 + (room + chunk - 1) // chunk]
+        torch.cuda.empty_cache()
+        yield
+    finally:
+        del hogs
+        gc.collect()
+        torch.cuda.empty_cache()
 
 
 def solve(sdp, inst):
@@ -34,22 +57,8 @@ def test_hsde_without_room_for_b(sdp, gpu):
         used = free0 - torch.cuda.mem_get_info()[0]
     assert 2 * b_bytes < used < 3 * b_bytes        # A and B are held
     print(f"held {used / 1e6:.0f} MB, A {b_bytes / 1e6:.0f} MB", flush=True)
-    chunk = 64 << 20
-    hogs = [torch.empty(torch.cuda.mem_get_info()[0] - (4 << 30), dtype=torch.uint8, device="cuda")]
-    try:
-        for _ in range(512):                       # (the device holds more than it reports free)
-            try:
-                hogs.append(torch.empty(chunk, dtype=torch.uint8, device="cuda"))
-            except torch.cuda.OutOfMemoryError:
-                break
-        print(f"{len(hogs) - 1} chunks", flush=True)
-        del hogs[1:1 + (used - b_bytes // 2 + chunk - 1) // chunk]
-        torch.cuda.empty_cache()
+    with fill_device(used - b_bytes // 2):
         got = solve(sdp, inst)
-    finally:
-        del hogs
-        gc.collect()
-        torch.cuda.empty_cache()
     for k in ("u", "y_dual", "X_packed", "L_packed"):
         assert rel_err(got[k], ref[k]) <= 1e-8, k
     assert not np.array_equal(got["u"], ref["u"])  # (the other form: other roundings)
