@@ -400,12 +400,17 @@ void enqueue_sequence(sdp_handle *h, hipStream_t st, int64_t n) {
   for (int64_t i = 0; i < n; ++i) enqueue_iteration(h, st, fold && i > 0, fold && i + 1 < n);
 }
 
-// The Jacobi variant of the unrolled iterations for blocks of N: their solves
-// start cold, where the most threads per block are fastest at every number of
-// cliques measured (400 blocks of 24: 165 us with 64 threads, 85 with 256 in
-// FP32, 340 and 193 in FP64; 3000: 309 and 298, 958 and 719; 400 of 56: 679
-// with 256, 539 with 512).  -1 where no kernel has eigenvectors.
-int unrolled_variant(int precision, int N) {
+// The Jacobi variant of the unrolled iterations for the plan's variant `planned`
+// of blocks of N: the two-level one where projection_method 2 planned it, else
+// scalar.  Their solves start cold, where the most threads per block are
+// fastest at every number of cliques measured (400 blocks of 24: 165 us with 64
+// threads, 85 with 256 in FP32, 340 and 193 in FP64; 3000: 309 and 298, 958 and
+// 719; 400 of 56: 679 with 256, 539 with 512), and the scalar variants faster
+// than the two-level ones but for few FP64 blocks of 80 (40 of 76: 4.8 ms scalar,
+// 3.5 two-level; 400 5.6 and 6.6; 40 FP32 blocks of 124 2.6 and 6.4).  -1 where
+// no kernel has eigenvectors.
+int unrolled_variant(int precision, int N, int planned, int method) {
+  if (method == 2 && projection_variant_two_level(precision, planned)) return planned;
   int best = -1, best_nt = 0;
   for (int v = 0; v < projection_variant_count(precision); ++v) {
     int n, nt;
@@ -435,7 +440,8 @@ void enqueue_unrolled_iteration(sdp_handle *h, hipStream_t st, void *eig, bool f
   // and the first pass must compute the same iterates bit for bit, or the
   // checkpoint spacing would change the result
   for (size_t b = 0; b < h->bucket_size.size(); ++b) {
-    const int v = unrolled_variant(h->precision, h->bucket_N[b]);
+    const int v = unrolled_variant(h->precision, h->bucket_N[b], h->bucket_size[b],
+                                   h->opt.projection_method);
     if (v < 0) fail(SDP_ERR_UNSUPPORTED, "no eigenvector kernel for this block size");
     HIPCHK(launch_admm_projection(h->precision, v, h->bucket_list[b], h->bucket_count[b], p, st));
   }
