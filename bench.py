@@ -80,7 +80,7 @@ def make_instances(name, batch_count):
     raise SystemExit(f"unknown workload {name}")
 
 
-def stage_bytes_flops(insts, precision, sweeps, algorithm="primal", cg_steps=0):
+def stage_bytes_flops(insts, precision, sweeps, algorithm="primal", cg_steps=0, part_bytes=0):
     """Algorithmic HBM bytes (or FLOPs) per launch of each stage, summed over
     the instances of the batch.  Dense A is streamed as B = L^-1 A (same size)
     and needs no triangular passes; sparse A is streamed as CSR (12 bytes per
@@ -93,7 +93,10 @@ def stage_bytes_flops(insts, precision, sweeps, algorithm="primal", cg_steps=0):
     With the conjugate-gradient affine step (cg_steps per iteration) A is
     streamed as itself; each step is one column pass (A^T p, written as
     W D^-1 A^T p), one row pass (A v) and the per-instance row-vector update
-    (11 row vectors of 8 bytes); the start reads r and diag and writes z, p."""
+    (11 row vectors of 8 bytes); the start reads r and diag and writes z, p.
+    With part_bytes > 0 (Solver.affine_plan) the dense instances' products take
+    one pass over B in stage A_v, which writes that many bytes of column sums for
+    AT_y to add up; Algorithm 3 then streams B too, and forms L^-1 nu_y in A_v."""
     import numpy as np
     tot = {k: 0 for k in ("scatter", "A_v", "Linv_r", "LinvT_y", "AT_y", "residual", "proj",
                           "cg_solve")}
@@ -110,6 +113,11 @@ def stage_bytes_flops(insts, precision, sweeps, algorithm="primal", cg_steps=0):
             tot["A_v"] += abytes + 8 * nnz + 16 * m
             tot["cg_solve"] += 32 * m + cg_steps * (2 * abytes + 32 * nnz + 104 * m)
             tot["AT_y"] += abytes + 8 * m + 32 * nnz
+        elif inst.a_format != 1 and part_bytes > 0:
+            tri = 8 * m * (m + 1) // 2 + 16 * m if algorithm == "hsde" else 0
+            tot["A_v"] += 8 * m * nnz + 8 * nnz + 16 * m + tri
+            tot["LinvT_y"] += tri
+            tot["AT_y"] += 24 * nnz
         elif inst.a_format == 1 or algorithm == "hsde":
             # sparse A, or the embedding (which keeps A and both triangular passes)
             abytes = 12 * int(inst.a_rowptr[-1]) if inst.a_format == 1 else 8 * m * nnz
@@ -122,6 +130,8 @@ def stage_bytes_flops(insts, precision, sweeps, algorithm="primal", cg_steps=0):
             bbytes = 8 * m * nnz
             tot["A_v"] += bbytes + 8 * nnz + 16 * m
             tot["AT_y"] += bbytes + 8 * m + 24 * nnz
+    tot["A_v"] += part_bytes
+    tot["AT_y"] += part_bytes
     d = {k: dict(bound="hbm", bytes=v) for k, v in tot.items() if k != "proj" and v > 0}
     d["projection"] = dict(bound="alu", flops=tot["proj"],
                            peak_tflops=FP32_VECTOR_TFLOPS if precision == "fp32"
@@ -474,6 +484,7 @@ def time_form(sdp, torch, insts, precision, steps, warmup, stage_iters, stream, 
         stages = {("cg_solve" if k == "Linv_r" else k): v for k, v in stages.items()
                   if k != "LinvT_y"}
     out["stages_ms"] = stages
+    out["affine_plan"] = S.affine_plan()
     S.close()
     return out
 
@@ -487,7 +498,7 @@ def batched_leg(args, sdp, torch, stream):
     steps = min(args.steps, 100)
     out = {"workload": WORKLOADS["batched"], "steps": steps, "warmup": args.warmup}
     keep = ("setup_s", "graph_chunk", "ms_per_step", "iter_per_s", "instance_iter_per_s",
-            "projections_per_s", "stages_ms", "solve")
+            "projections_per_s", "stages_ms", "affine_plan", "solve")
     for precision in ("fp32", "fp64"):
         print(f"[bench] batched {precision}: timing", file=sys.stderr, flush=True)
         f = time_form(sdp, torch, insts, precision, steps, args.warmup, args.stage_iters, stream,
@@ -497,7 +508,8 @@ def batched_leg(args, sdp, torch, stream):
             # the longest stage of the batched FP32 iteration, with the counter
             # traffic of profiles/traffic_batched.json when it is current
             out["roofline"] = roofline_of(insts, f["stages_ms"], f["timed_sweeps_per_projection"],
-                                          "primal", solver_options(args), "batched")
+                                          "primal", solver_options(args), "batched",
+                                          f["affine_plan"]["part_bytes"])
         print(f"[bench] batched {precision}: {f['iter_per_s']:.1f} batched iter/s",
               file=sys.stderr, flush=True)
     print("[bench] batched: loop of per-instance FP64 solves", file=sys.stderr, flush=True)
@@ -574,12 +586,12 @@ def time_adjoint(sdp, torch, insts, precision, T, ckpt, stream):
     return out, cb.cpu().numpy(), bb.cpu().numpy()
 
 
-def roofline_of(insts, stages_ms, sweeps, algorithm, extra, workload):
+def roofline_of(insts, stages_ms, sweeps, algorithm, extra, workload, part_bytes=0):
     """Roofline of the longest stage: algorithmic bytes (or flops) per launch
     over its mean launch time, with the counter traffic of the workload's
     profile when one is committed for the current kernel source."""
     model = stage_bytes_flops(insts, "fp32", sweeps, algorithm,
-                              cg_steps=extra.get("cg_max_iter", 0))
+                              cg_steps=extra.get("cg_max_iter", 0), part_bytes=part_bytes)
     stages = {k: v for k, v in stages_ms.items() if k in model}
     dom = max(stages, key=lambda k: stages[k])
     t_launch = stages[dom] / 1e3
@@ -796,7 +808,7 @@ def main():
     head = forms["fp32"]
     extra = solver_options(args)
     roof = roofline_of(insts, head["stages_ms"], head["timed_sweeps_per_projection"],
-                       args.algorithm, extra, args.workload)
+                       args.algorithm, extra, args.workload, head["affine_plan"]["part_bytes"])
 
     cpu = None
     if not args.no_cpu_baseline:
@@ -1012,8 +1024,9 @@ def run_adjoint(args, sdp, torch, insts, stream):
         sweeps = ((st1["jacobi_sweeps"] - st0["jacobi_sweeps"]) /
                   max(st1["projections"] - st0["projections"], 1))
         stages = S.time_stages(20)
+        part_bytes = S.affine_plan()["part_bytes"]
         S.close()
-    roof = roofline_of(insts, stages, sweeps, "primal", {}, "adjoint")
+    roof = roofline_of(insts, stages, sweeps, "primal", {}, "adjoint", part_bytes)
     roof["note"] = "longest stage of the forward iteration (the reverse sweep reuses the same passes)"
     cpu = None
     if not args.no_cpu_baseline:

@@ -342,9 +342,18 @@ int sdp_projection_plan(sdp_handle *h, int32_t cap, int32_t *block_n, int32_t *t
  * precision) of each launch list of sdp_projection_plan, same order. */
 int sdp_projection_plan_variants(sdp_handle *h, int32_t cap, int32_t *variant, int32_t *count);
 
+/* How the handle's dense instances take both products with B = L^-1 A: in one
+ * pass over it (*workgroups > 0: its workgroups, *part_bytes the column sums
+ * it writes and the next launch adds up) or in two (both 0).  *passes counts the
+ * one-pass launches completed since setup.  Any pointer may be NULL.
+ * Synchronises. */
+int sdp_affine_plan(sdp_handle *h, int32_t *workgroups, int64_t *part_bytes, int64_t *passes);
+
 /* Times every stage of the iteration on its own: stage s is launched n_iter
  * times back to back between two HIP events on the handle's stream (stages
- * in iteration order), and ms[s] receives the mean milliseconds per launch:
+ * in iteration order; the pass of sdp_affine_plan together with stage 4, which
+ * it needs between its launches, and stage 4's own mean taken off), and ms[s]
+ * receives the mean milliseconds per launch:
  * 0 scatter (bhat), 1 A v - b (B v - L^-1 b for dense A), 2 L^-1 r, 3 L^-T y1
  * (2 and 3 only for sparse-A instances), 4 u = (bhat - A^T y)/D, 5 clique
  * projections with the multiplier update (all launch lists), 6 residual

@@ -75,7 +75,7 @@ EXPORTS = ["sdp_default_options", "sdp_setup", "sdp_reset", "sdp_admm_step", "sd
            "sdp_psd_project_batched", "sdp_projection_variants", "sdp_psd_project_variant",
            "sdp_get_solution", "sdp_set_state", "sdp_get_history",
            "sdp_diagnostics", "sdp_diagnostics_noalloc", "sdp_get_stats",
-           "sdp_get_projection_stats", "sdp_projection_plan", "sdp_time_stages",
+           "sdp_get_projection_stats", "sdp_projection_plan", "sdp_affine_plan", "sdp_time_stages",
            "sdp_update_data", "sdp_set_unrolled_records", "sdp_unrolled_forward", "sdp_vjp", "sdp_cg_steps", "sdp_destroy",
            "sdp_projection_variant_kind", "sdp_projection_plan_variants",
            "sdp_projection_default_variant", "sdp_sign_schedule",
@@ -113,6 +113,7 @@ def _load():
     lib.sdp_get_projection_stats.argtypes = [_p] + [C.POINTER(C.c_int64)] * 3
     ip = C.POINTER(C.c_int32)
     lib.sdp_projection_plan.argtypes = [_p, C.c_int32, ip, ip, ip, ip]
+    lib.sdp_affine_plan.argtypes = [_p, ip, C.POINTER(C.c_int64), C.POINTER(C.c_int64)]
     lib.sdp_time_stages.argtypes = [_p, C.c_int32, dp]
     lib.sdp_update_data.argtypes = [_p, _p, _p]
     lib.sdp_set_unrolled_records.argtypes = [_p, C.c_int64]
@@ -356,6 +357,13 @@ class Solver:
         N, NT, cnt = (C.c_int32 * k)(), (C.c_int32 * k)(), (C.c_int32 * k)()
         _check(lib.sdp_projection_plan(self._h, k, N, NT, cnt, C.byref(n)))
         return [(N[i], NT[i], cnt[i]) for i in range(k)]
+
+    def affine_plan(self):
+        """Workgroups and bytes of column sums of the one-pass products with B
+        (0: two passes), and how many such passes completed."""
+        wg, pb, n = C.c_int32(0), C.c_int64(0), C.c_int64(0)
+        _check(lib.sdp_affine_plan(self._h, C.byref(wg), C.byref(pb), C.byref(n)))
+        return dict(workgroups=wg.value, part_bytes=pb.value, passes=n.value)
 
     def projection_plan_variants(self):
         """Kernel variant index of each projection launch list."""

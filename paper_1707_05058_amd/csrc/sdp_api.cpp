@@ -282,6 +282,7 @@ struct sdp_handle {
   int n_t_rows_all = 0;
   int32_t *d_t_rows_dense = nullptr;     // (inst, row) over the rows of dense instances
   int n_t_rows_dense = 0;
+  int64_t fu_part_doubles = 0;           // partial sums of the fused pass
   double *d_ytmp = nullptr;              // row-space scratch for the scaled multiplier
   double *d_utmp = nullptr;              // coordinate scratch (Algorithm 2: -rho x)
   // affine step by conjugate gradients (no factor)
@@ -1118,6 +1119,7 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
       a.fu_slots = dev_zeros<unsigned long long>(fused_slots_per_row() * row, own);
       a.fu_tag = dev_upload(std::vector<uint32_t>(1, 1u), own);   // (cleared slots: tag 0)
       a.fu_part = dev_zeros<double>(fp.part_doubles, own);
+      h->fu_part_doubles = fp.part_doubles;
       a.fu_part_first = dev_upload(fp.part_first, own);
     }
     a.csr_rows = dev_upload(csr_rows, own);
@@ -1813,6 +1815,22 @@ int sdp_projection_plan(sdp_handle *h, int32_t cap, int32_t *block_n, int32_t *t
   });
 }
 
+int sdp_affine_plan(sdp_handle *h, int32_t *workgroups, int64_t *part_bytes, int64_t *passes) {
+  return guarded([&] {
+    if (!h) fail(SDP_ERR_ARG, "NULL handle");
+    const bool fused = h->aff.fu_ntiles > 0 && h->aff.Bm;
+    uint32_t tag = 1;   // of the next pass; the first is 1
+    if (fused) {
+      HIPCHK(hipMemcpyAsync(&tag, h->aff.fu_tag, sizeof(tag), hipMemcpyDeviceToHost, h->stream));
+      HIPCHK(hipStreamSynchronize(h->stream));
+    }
+    if (workgroups) *workgroups = fused ? h->aff.fu_ntiles : 0;
+    if (part_bytes) *part_bytes = fused ? 8 * h->fu_part_doubles : 0;
+    if (passes) *passes = (int64_t)(tag - 1u);
+    return SDP_OK;
+  });
+}
+
 int sdp_time_stages(sdp_handle *h, int32_t n_iter, double *ms) {
   return guarded([&] {
     if (!h || n_iter <= 0 || !ms) fail(SDP_ERR_ARG, "invalid arguments");
@@ -1820,6 +1838,11 @@ int sdp_time_stages(sdp_handle *h, int32_t n_iter, double *ms) {
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
+    // The fused pass exchanges parts of its sums through words tagged with a
+    // number that stage 4 advances: launched back to back its members would find
+    // the words of the launch before and wait for nobody.  So it is timed
+    // together with stage 4, whose own time is then taken off.
+    const bool fused = h->aff.fu_ntiles > 0 && h->aff.Bm;
     try {
       for (int s = 0; s < NS; ++s) {
         HIPCHK(hipEventRecord(e0, h->stream));
@@ -1829,6 +1852,7 @@ int sdp_time_stages(sdp_handle *h, int32_t n_iter, double *ms) {
               HIPCHK(launch_hsde_start(h->hsa, h->stream));
             } else if (s < 5) {
               hsde_affine(h, h->aff, s, h->stream);
+              if (fused && s == 1) HIPCHK(launch_affine_stage(h->aff, 4, h->stream));
             } else if (s == 5) {
               HIPCHK(launch_hsde_update(h->hsa, h->stream));
               enqueue_projections(h, h->proj, h->stream);
@@ -1839,7 +1863,8 @@ int sdp_time_stages(sdp_handle *h, int32_t n_iter, double *ms) {
           }
           if (s < 5) {
             if (!h->cg) HIPCHK(launch_affine_stage(h->aff, s, h->stream));
-            else if (s != 3) HIPCHK(launch_cg_stage(h->aff, s, h->stream));
+            if (fused && s == 1) HIPCHK(launch_affine_stage(h->aff, 4, h->stream));
+            if (h->cg && s != 3) HIPCHK(launch_cg_stage(h->aff, s, h->stream));
           } else if (s == 5) {
             // (the launches step through the re-orthonormalisation period as
             // the iterations do; the iteration counter itself does not move)
@@ -1857,6 +1882,7 @@ int sdp_time_stages(sdp_handle *h, int32_t n_iter, double *ms) {
         HIPCHK(hipEventElapsedTime(&t, e0, e1));
         ms[s] = (double)t / n_iter;
       }
+      if (fused) ms[1] -= ms[4];
     } catch (...) {
       (void)hipEventDestroy(e0);
       (void)hipEventDestroy(e1);
