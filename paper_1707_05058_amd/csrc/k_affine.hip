@@ -1032,13 +1032,13 @@ hipError_t launch_objective(const AffineArgs &a, double *obj, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The fused pass's tiles for the dense instances (m, ld) of a handle: empty
-// where it would not pay.  A cluster of G = ceil(ld / FU_COLS) workgroups
-// takes a group of rows; one workgroup runs per compute unit, so the groups
-// are as long as fills the chip once (256 workgroups).
-FusedPlan plan_fused(const std::vector<InstDesc> &inst) {
-  constexpr int UNITS = 256;
+// The fused pass's tiles for the dense instances (m, ld) of a handle on a device
+// of `units` compute units: empty where it would not pay.  A cluster of G =
+// ceil(ld / FU_COLS) workgroups takes a group of rows; one workgroup runs per
+// unit, so the groups are as long as fills the chip once.
+FusedPlan plan_fused(const std::vector<InstDesc> &inst, int units) {
   FusedPlan p;
+  if (units < 1) return p;
   int64_t chunks = 0, bytes = 0, most = 1;
   for (const InstDesc &d : inst) {
     if (d.a_format != 0 || d.m <= 0) continue;
@@ -1059,10 +1059,14 @@ FusedPlan plan_fused(const std::vector<InstDesc> &inst) {
   // time: with more, they start when units fall free, and members waiting for
   // one another (then computing the missing parts) took 50 ms for the 31.8 GB of
   // 512 instances, against 9.5 in two passes.
-  int64_t rows = std::max<int64_t>((chunks + UNITS - 1) / UNITS, 1);
-  while (rows < most && count(rows) > UNITS) ++rows;
-  // (with less than 60% of the units' rows in use, two passes are no slower)
-  if (count(rows) > UNITS || 10 * chunks < 6 * UNITS * rows) return FusedPlan();
+  int64_t rows = std::max<int64_t>((chunks + units - 1) / units, 1);
+  while (rows < most && count(rows) > units) ++rows;
+  // With less than 60% of the units' rows in use the gain shrinks to nothing for
+  // some shapes (instances of 41 rows and 4335 columns, us per iteration in one
+  // pass / two: 70 of them, 55% in use, 125 / 125; 52 110 / 116; 85, 66%, 130 /
+  // 134; 100 135 / 146).  (Others still gain there: 52 of 300 rows and 3903
+  // columns 130 / 208, 60 166 / 286.)
+  if (count(rows) > units || 10 * chunks < 6 * (int64_t)units * rows) return FusedPlan();
   p.part_first.assign(2 * inst.size(), 0);
   for (size_t i = 0; i < inst.size(); ++i) {
     const InstDesc &d = inst[i];

@@ -1093,7 +1093,10 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     h->d_t_rows_all = dev_upload(t_rows_all, own);
     h->n_t_rows_all = (int)(t_rows_all.size() / 2);
     h->d_ytmp = dev_zeros<double>(row, own);
-    const FusedPlan fp = d_A && !cg && may_fuse ? plan_fused(h->desc) : FusedPlan();
+    int dev = 0, units = 0;
+    HIPCHK(hipStreamGetDevice(h->stream, &dev));
+    HIPCHK(hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev));
+    const FusedPlan fp = d_A && !cg && may_fuse ? plan_fused(h->desc, units) : FusedPlan();
     one_pass = !fp.tiles.empty();
     if (opt.algorithm == SDP_ALG_HSDE) {
       // the embedding needs g = L^-T y1 itself on every row; its right-hand

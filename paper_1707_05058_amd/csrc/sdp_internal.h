@@ -305,7 +305,7 @@ struct FusedPlan {
   std::vector<int64_t> part_first;            // 2 per instance
   int64_t part_doubles = 0;
 };
-FusedPlan plan_fused(const std::vector<InstDesc> &inst);   // no tiles where it does not pay
+FusedPlan plan_fused(const std::vector<InstDesc> &inst, int units);   // no tiles where it does not pay
 int64_t fused_slots_per_row();
 hipError_t launch_iteration_affine(const AffineArgs &a, hipStream_t st);
 // The affine step with conjugate gradients: scatter, r0, the solve, u.
