@@ -131,7 +131,7 @@ typedef struct {
                                    with autotune = 0, the default variant) chooses, and the
                                    cliques listed under 3 take the sign function; 1 scalar parallel-order Jacobi only (FP64
                                    cliques of 97-128 still take the sign function, the only
-                                   kernel for them); 2 the two-level (block) Jacobi wherever a
+                                   kernel for them; see decouple for FP32); 2 the two-level (block) Jacobi wherever a
                                    variant for the clique size exists (blocks of 64 and more),
                                    scalar elsewhere; 3 the matrix sign function, X_k = (W + W sign(W)) / 2 (no eigenvectors, no
                                    warm start), for cliques of up to 32 vertices (in one
@@ -151,7 +151,12 @@ typedef struct {
                                    basis.  A clique whose attempts keep failing is projected
                                    by the matrix sign function and tries again only in the
                                    iterations 64, 128, 256, 512 and every 512th after
-                                   that.  The
+                                   that.  With projection_method = 1 the sweeps project it,
+                                   it tries from the first iteration on and skips the
+                                   attempt for 4 iterations after a failure, doubling after each
+                                   further one in a row, up to 64, and only blocks of up to 96 with
+                                   two or more failures in a row use the sign function
+                                   while they wait.  The
                                    result is P+(W) to the sweep tolerance either way.  With
                                    projection_method = 0 those blocks then take the scalar
                                    variants (which carry the decoupling).  Ignored for FP64

@@ -43,6 +43,7 @@ namespace {
 // little room (||T||_F <= 3.4e-4).
 enum Mode { MODE_ADMM = 0, MODE_STANDALONE = 1, MODE_MINEIG = 2, MODE_ADMM_DEC = 3 };
 constexpr int DEC_MIN_N = 64;
+constexpr int DEC_BACK_OFF_SIGN_N = 96;
 
 // When a clique takes the decoupling: one double per clique (its partial-sum
 // slot 7), 64 times the iterations since the record was cleared plus m.  m = 0:
@@ -78,6 +79,29 @@ struct DecState {
     return (double)((it + 1) * 64 + m);
   }
 };
+
+// The same record under projection_method 1 (Jacobi): 256 level + the iterations
+// that the clique still skips the attempt, sweeping instead; 4 after a failure,
+// doubling with every further one in a row up to 64.  Blocks of up to 96 with two
+// failures in a row or more take the sign function while they wait; for larger
+// ones it never takes the place of the sweeps.
+struct DecBackOff {
+  int level;
+  double wait;
+  __device__ explicit DecBackOff(double v) : level((int)(v * (1.0 / 256.0))), wait(v - 256.0 * level) {}
+  __device__ bool waits() const { return wait > 0.0; }
+  __device__ bool sign(int n) const { return waits() && level >= 2 && n <= DEC_BACK_OFF_SIGN_N; }
+  __device__ double after_wait() const { return 256.0 * level + wait - 1.0; }
+  __device__ double after_attempt(bool ok) const {
+    const int nl = level < 5 ? level + 1 : 5;
+    return ok ? 0.0 : 256.0 * nl + (double)(4 << (nl - 1));
+  }
+};
+
+// Whether k_sign_big projects the clique of record v, of padded size n, now.
+__device__ inline bool dec_takes_sign(const ProjArgs &a, double v, int n) {
+  return a.dec_back_off ? DecBackOff(v).sign(n) : DecState(v).sign();
+}
 
 template <typename T> struct Num;
 template <> struct Num<float> {
@@ -688,10 +712,11 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
   double dec_rec = 0.0;
   if constexpr (DEC) {
     dec_rec = a.part[NPART * (int64_t)cl + 7];
-    if (DecState(dec_rec).sign()) {   // k_sign_big has projected it (uniform)
-      __syncthreads();                // every thread has read the record
+    if (dec_takes_sign(a, dec_rec, N)) {   // k_sign_big has projected it (uniform)
+      __syncthreads();                     // every thread has read the record
       if (tid == 0 && !inst_done)
-        a.part[NPART * (int64_t)cl + 7] = DecState(dec_rec).after_sign();
+        a.part[NPART * (int64_t)cl + 7] = a.dec_back_off ? DecBackOff(dec_rec).after_wait()
+                                                         : DecState(dec_rec).after_sign();
       return;
     }
   }
@@ -845,9 +870,15 @@ __global__ __launch_bounds__(NT) void k_project(ProjArgs a, const int32_t *__res
   // whose eigenvectors are not recorded)
   bool dec = false;
   if constexpr (DEC) {
-    dec = decouple_blocks<T, N, NT, P>(A, V, Abuf, Vbuf, th, red, thr, a.dec_tmax2, a.dec_max_ref);
+    const bool waits = a.dec_back_off && DecBackOff(dec_rec).waits();   // (uniform)
+    if (!waits)
+      dec = decouple_blocks<T, N, NT, P>(A, V, Abuf, Vbuf, th, red, thr, a.dec_tmax2,
+                                         a.dec_max_ref);
     // (every thread read the clique's record before the gather's barriers)
-    if (tid == 0) a.part[NPART * (int64_t)cl + 7] = DecState(dec_rec).after_attempt(dec);
+    if (tid == 0)
+      a.part[NPART * (int64_t)cl + 7] = !a.dec_back_off ? DecState(dec_rec).after_attempt(dec)
+                                        : waits         ? DecBackOff(dec_rec).after_wait()
+                                                        : DecBackOff(dec_rec).after_attempt(dec);
   }
 
   int sweep = 0;
@@ -2415,7 +2446,7 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
     rho = a.state[inst].rho;
     if (MODE == 3) hf = a.hs[inst].f;
     // beside the decoupling: only the cliques that do not take it (uniform)
-    if (a.sign_rest && !DecState(a.part[NPART * (int64_t)cl + 7]).sign()) return;
+    if (a.sign_rest && !dec_takes_sign(a, a.part[NPART * (int64_t)cl + 7], N)) return;
   }
   // packed position of (i, j) in the clique's lower triangle (i, j < s)
   const auto packed = [&](int i, int j) {
@@ -3217,7 +3248,8 @@ hipError_t launch_admm_projection(int precision, int variant, const int32_t *lis
   }
   const int blk = projection_variant_two_level(precision, variant);
   if (a.decouple && a.vw && !a.eig) {
-    if (precision == 1 && !blk && N >= DEC_MIN_N) {
+    if (precision == 1 && !blk && N >= DEC_MIN_N &&
+        !(a.dec_back_off && N > DEC_BACK_OFF_SIGN_N)) {
       ProjArgs w = a;   // the cliques that do not take the decoupling now
       w.sign_rest = 1;
       const hipError_t e = launch_sign_big<float>(N, list, count, w, sign_plan(a.tol, N), st);

@@ -1149,6 +1149,7 @@ void setup_impl(int32_t batch, const sdp_instance *inst, const sdp_options *opt_
     p.max_sweeps = h->max_sweeps;
     p.tol = h->jac_tol;
     p.decouple = opt.decouple && h->precision == SDP_FP32_EIG;
+    p.dec_back_off = opt.projection_method == 1;
     p.dec_max_ref = h->precision == SDP_FP32_EIG ? 2 : 3;
     // the rotation Q = I + T + T^2 / 2 has Q^T Q - I = T^4 / 4, at most
     // ||T||_F^4 / 4: with ||T||_F^2 <= sqrt(tol / 0.75) that stays below a

@@ -99,6 +99,7 @@ struct ProjArgs {
   // positive/negative decoupling of warm-started blocks: on/off, refinements
   // per attempt, bound on ||T||_F^2 for one Newton-Schulz step
   int decouple, dec_max_ref;
+  int dec_back_off;       // projection_method 1: sweeps after a failed attempt, not the sign function
   int sign_rest;          // k_sign_big: only the cliques that do not take the decoupling now
   double dec_tmax2;
   void *eig;              // optional: per clique V (s x N) then theta (N), precision T
