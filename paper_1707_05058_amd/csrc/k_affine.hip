@@ -1092,9 +1092,14 @@ int affine_col_tile_width() { return COL_W; }
 int affine_cg_tile_rows() { return CG_ROWS; }
 int affine_csc_tile_width() { return CSC_COLS; }
 // Consecutive rows per wave of the sparse row products: several where rows
-// are short and there are enough of them to fill the chip.
+// are short and there are enough of them to fill the chip.  Iterations of three
+// conjugate-gradient steps over 320 000 coordinates, us, one row a wave / four:
+// 17 000 rows of 16 265 / 262, of 64 282 / 283, of 96 302 / 307; 40 000 of 4 289 /
+// 273, of 64 353 / 343, of 80 379 / 382, of 96 396 / 406, of 128 437 / 445; 100 000
+// of 16 404 / 352, of 64 541 / 503, of 80 630 / 614, of 96 715 / 721, of 256 1740 /
+// 1823.
 int affine_csr_rows_per_wave(int64_t rows, int64_t nnz) {
-  return rows >= 16384 && nnz <= 128 * rows ? CSR_R : 1;
+  return rows >= 16384 && nnz <= 64 * rows ? CSR_R : 1;
 }
 int affine_max_rows_per_tile() { return MAX_R; }
 
