@@ -240,9 +240,10 @@ int sdp_projection_variants(int32_t dtype, int32_t cap, int32_t *block_n, int32_
  *              round-robin, each pair's 16 x 16 problem diagonalised by one
  *              wave and applied to the block on the matrix cores;
  *   *kind = 2  matrix sign function, P+(W) = (W + W sign(W)) / 2, sign(W) by
- *              polynomial iterations on the matrix cores (k1 steps of
- *              X (3I - 3.2X^2 + 1.2X^4), then k2 of X (3I - X^2) / 2, as
- *              sdp_sign_schedule gives them).  It yields no eigenvectors: the
+ *              polynomial iterations on the matrix cores (fast steps
+ *              X (3I - 3.2X^2 + 1.2X^4), then finishing steps, as
+ *              sdp_sign_plan and sdp_sign_schedule give them).  It yields no
+ *              eigenvectors: the
  *              standalone projections run it, and the solver's plans
  *              (projection_method 0 or 3) for cliques of up to 32 vertices
  *              (the one-wave variants of 16 and 32), in SDP_FP64 for all
@@ -260,10 +261,22 @@ int sdp_projection_variant_kind(int32_t dtype, int32_t variant, int32_t *kind);
  * eigenvalue follows the scalar maps; the bound takes n - 1 eigenvalues at
  * the worst point of a fine grid).  FP32-eig's default tolerance 1e-6 gives
  * (12, 2) for n = 16; FP64's 1e-14 gives (29, 2).  Tolerances below 1e-16
- * are taken as 1e-16.  This is the worst case over all spectra: the kernels
- * stop earlier once ||I - X^2||_F shows every eigenvalue near +-1.
+ * are taken as 1e-16.  This is the worst case over all spectra, which the split
+ * iteration of a few large FP64 cliques, the LDS kernel of 32 vertices and 256
+ * threads and, unless they stop early, the solver's launches of up to 4096
+ * FP32 cliques of up to 16 vertices take.
  * SDP_ERR_ARG if n < 1 or a pointer is NULL. */
 int sdp_sign_schedule(double tol, int32_t n, int32_t *k1, int32_t *k2);
+
+/* The steps of the other sign-function kernels (host only): at most *k1 fast
+ * steps, the first of c X0 with c = 1.25 / ||X0^2||_F^(1/2) >= 1.25, then *k2 fitted
+ * finishing steps x <- x (b0 + b1 r + b2 r^2), r = 1 - x^2, of three products:
+ * (1.002014, 0.523437, 0.325222), then (1, 1/2 + 0.9375 0.00338^2, 3/8), then
+ * (1, 1/2, 3/8).  Once ||I - X^2||_F <= 0.9 is seen after k fast steps, one more
+ * fast step and stop[k] (32 entries; 0: go on) fitted ones end the iteration.
+ * For every spectrum the error stays within tol ||W||_F / 2, after a stop within
+ * a third of that (or 1.5e-16 an eigenvalue).  SDP_ERR_ARG if n < 1 or a pointer is NULL. */
+int sdp_sign_plan(double tol, int32_t n, int32_t *k1, int32_t *k2, int32_t *stop);
 
 /* The variant sdp_psd_project_batched runs for blocks of up to max_size
  * (host only): the sign-function variant of the smallest block size that

@@ -78,7 +78,7 @@ EXPORTS = ["sdp_default_options", "sdp_setup", "sdp_reset", "sdp_admm_step", "sd
            "sdp_get_projection_stats", "sdp_projection_plan", "sdp_affine_plan", "sdp_time_stages",
            "sdp_update_data", "sdp_set_unrolled_records", "sdp_unrolled_forward", "sdp_vjp", "sdp_cg_steps", "sdp_destroy",
            "sdp_projection_variant_kind", "sdp_projection_plan_variants",
-           "sdp_projection_default_variant", "sdp_sign_schedule",
+           "sdp_projection_default_variant", "sdp_sign_schedule", "sdp_sign_plan",
            "sdp_last_error",
            "sdp_pattern_create", "sdp_pattern_sizes", "sdp_pattern_get", "sdp_pattern_destroy",
            "sdp_scale_compute", "sdp_scale_apply", "sdp_scale_recover"]
@@ -124,6 +124,7 @@ def _load():
     lib.sdp_projection_default_variant.argtypes = [C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
     lib.sdp_sign_schedule.argtypes = [C.c_double, C.c_int32, C.POINTER(C.c_int32),
                                       C.POINTER(C.c_int32)]
+    lib.sdp_sign_plan.argtypes = [C.c_double, C.c_int32] + [C.POINTER(C.c_int32)] * 3
     lib.sdp_projection_plan_variants.argtypes = [_p, C.c_int32, ip, C.POINTER(C.c_int32)]
     lib.sdp_destroy.argtypes = [_p]
     lib.sdp_destroy.restype = None
@@ -451,6 +452,15 @@ def sign_schedule(tol: float, n: int):
     k1, k2 = C.c_int32(0), C.c_int32(0)
     _check(lib.sdp_sign_schedule(float(tol), int(n), C.byref(k1), C.byref(k2)))
     return k1.value, k2.value
+
+
+def sign_plan(tol: float, n: int):
+    """(k1, k2, stop): most fast and finishing steps of the kernels that stop
+    early, and stop[k] finishing steps after one more fast step where they stop
+    after k (include/sdp.h)."""
+    k1, k2, stop = C.c_int32(0), C.c_int32(0), (C.c_int32 * 32)()
+    _check(lib.sdp_sign_plan(float(tol), int(n), C.byref(k1), C.byref(k2), stop))
+    return k1.value, k2.value, list(stop)
 
 
 def projection_default_variant(dtype: int, max_size: int) -> int:

@@ -30,6 +30,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <stdexcept>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -1544,6 +1545,8 @@ __global__ __launch_bounds__(256) void k_identity_bases(T *vw, const int64_t *vw
 // bound, and 1024 uniform points on (0, 1] (e is smooth; the factor 2 covers
 // the grid and rounding).  Tolerances below 1e-16, beyond what FP64 products
 // resolve, are taken as 1e-16.
+constexpr int SIGN_K1_MAX = 200;
+
 void sign_schedule(double tol, int n, int *k1_out, int *k2_out) {
   static std::mutex mu;
   static std::map<std::pair<double, int>, std::pair<int, int>> cache;
@@ -1558,9 +1561,9 @@ void sign_schedule(double tol, int n, int *k1_out, int *k2_out) {
     for (int j = 0; j <= 256 * dec; ++j) d.push_back(std::pow(10.0, -dec + j / 256.0));
     for (int j = 1; j <= 1024; ++j) d.push_back(j / 1024.0);
     std::vector<double> x(d), y(d.size());
-    constexpr int K1_MAX = 200, K2_MAX = 8;
-    int best = INT_MAX, b1 = K1_MAX, b2 = 4;
-    for (int k1 = 0; k1 <= K1_MAX && 3 * k1 + 4 < best; ++k1) {
+    constexpr int K2_MAX = 8;
+    int best = INT_MAX, b1 = SIGN_K1_MAX, b2 = 4;
+    for (int k1 = 0; k1 <= SIGN_K1_MAX && 3 * k1 + 4 < best; ++k1) {
       if (k1 > 0)
         for (double &v : x) v = v * (3.0 - 3.2 * v * v + 1.2 * v * v * v * v);
       y = x;
@@ -1591,7 +1594,7 @@ void sign_schedule(double tol, int n, int *k1_out, int *k2_out) {
 // SIGN_THETA, so only the starting points x_0 of the grid whose scalar
 // iterates do are left, and the bound 2 sqrt(n - 1) max e <= tol of
 // sign_schedule is taken over those, with tol / 3, which keeps stopping early
-// from using the budget up.
+// from using the budget up (no stop at a k for which no count meets it).
 // (The first step scales X0 by c >= SIGN_X_MAX: an eigenvalue delta starts at
 // x_0 = c delta, and |x_0| |1 - s| / 2 bounds its error.)
 SignPlan sign_plan(double tol, int n) {
@@ -1616,10 +1619,10 @@ SignPlan sign_plan(double tol, int n) {
     return v * (p.b0 + r * (p.b1 + r * p.b2));
   };
   // finishing steps after which the starting points marked in `in` meet the
-  // bound from the iterates x (`most` if that takes more)
+  // bound from the iterates x (0: more than `most`)
   const auto steps = [&](std::vector<double> x, const std::vector<char> &in, int most,
                          double bound) {
-    for (int n2 = 1; n2 < most; ++n2) {
+    for (int n2 = 1; n2 <= most; ++n2) {
       double e = 0.0;
       for (size_t j = 0; j < d.size(); ++j) {
         x[j] = finish(x[j], n2 - 1);
@@ -1627,7 +1630,7 @@ SignPlan sign_plan(double tol, int n) {
       }
       if (e <= bound) return n2;
     }
-    return most;
+    return 0;
   };
   std::vector<double> x(d);
   std::vector<char> in(d.size());
@@ -1638,9 +1641,14 @@ SignPlan sign_plan(double tol, int n) {
     // (1.5e-16: what the double-precision iterates resolve)
     pl.set_steps_after(k, steps(x, in, 15, std::max(target / 3, std::min(target, 1.5e-16))));
   }
-  // the worst case from the scaled start (x_0 up to SIGN_X_MAX)
+  // the worst case from the scaled start (x_0 up to SIGN_X_MAX); more fast steps
+  // where the finishing steps alone do not reach the bound
   std::fill(in.begin(), in.end(), 1);
-  pl.k2 = steps(x, in, 12, target);
+  while ((pl.k2 = steps(x, in, 12, target)) == 0) {
+    if (pl.k1 >= 2 * SIGN_K1_MAX) throw std::runtime_error("no sign iteration for this tolerance");
+    for (double &v : x) v = fast(v);
+    ++pl.k1;
+  }
   cache.emplace(key, pl);
   return pl;
 }

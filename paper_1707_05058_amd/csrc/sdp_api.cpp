@@ -1580,6 +1580,17 @@ int sdp_sign_schedule(double tol, int32_t n, int32_t *k1, int32_t *k2) {
   });
 }
 
+int sdp_sign_plan(double tol, int32_t n, int32_t *k1, int32_t *k2, int32_t *stop) {
+  return guarded([&] {
+    if (!k1 || !k2 || !stop || n < 1) fail(SDP_ERR_ARG, "invalid arguments");
+    const SignPlan pl = sign_plan(tol, n);
+    *k1 = pl.k1;
+    *k2 = pl.k2;
+    for (int k = 0; k < SignPlan::KMAX; ++k) stop[k] = pl.steps_after(k);
+    return SDP_OK;
+  });
+}
+
 int sdp_projection_default_variant(int32_t dtype, int32_t max_size, int32_t *variant) {
   return guarded([&] {
     if (dtype != SDP_DTYPE_FP64 && dtype != SDP_DTYPE_FP32) fail(SDP_ERR_ARG, "invalid dtype");
