@@ -878,18 +878,24 @@ PROJ_SIZES = (15, 16, 24, 32, 50, 64, 96, 128)
 
 def sign_products(sdp, prec, N, threads):
     """Matrix-core flops of one sign-function projection of a padded N x N
-    block: the library's schedule (sdp.sign_schedule) of k1 fast steps of
-    three products, k2 Newton-Schulz steps of two, one final product, at
-    2 N 16^2 flops per 16 x 16 tile; the LDS kernels form the TN (TN + 1) / 2
-    tiles on or below the diagonal, the one-wave register kernels for N = 32
-    all TN^2 (each off-diagonal tile is the other's operand).  That is the
-    schedule for the worst spectrum; the kernels stop once the iterate is near
-    (N(0,1) blocks: about half of it in FP32, a quarter to a third in FP64)."""
+    block whose spectrum takes every step: k1 fast steps of three products, k2
+    finishing steps (sdp.sign_plan: three products each; the kernel of 32
+    vertices and 256 threads sdp.sign_schedule's Newton-Schulz steps of two),
+    one final product, at 2 N 16^2 flops per 16 x 16 tile; the LDS kernels form
+    the TN (TN + 1) / 2 tiles on or below the diagonal, the one-wave register
+    kernels for N = 32 all TN^2 (each off-diagonal tile is the other's operand).
+    Blocks that come near earlier stop (N(0,1) ones after about half of it in
+    FP32, a quarter to a third in FP64), so no rate follows from it."""
     tol = 1e-6 if prec == "fp32" else 1e-14
-    k1, k2 = sdp.sign_schedule(tol, N)
+    if (N, threads) == (32, 256):
+        k1, k2 = sdp.sign_schedule(tol, N)
+        products = 3 * k1 + 2 * k2 + 1
+    else:
+        k1, k2, _ = sdp.sign_plan(tol, N)
+        products = 3 * (k1 + k2) + 1
     tn = N // 16
     tiles = tn * tn if (N == 32 and threads == 64) else tn * (tn + 1) // 2
-    return (3 * k1 + 2 * k2 + 1) * tiles * 2 * N * 16 * 16
+    return products * tiles * 2 * N * 16 * 16
 
 
 def run_projection(args, sdp, torch, stream):
@@ -941,9 +947,9 @@ def run_projection(args, sdp, torch, stream):
             # the variant the library runs without an explicit choice
             dv = sdp.projection_default_variant(dtc, s)
             model = 10.0 * s ** 3 * count
-            executed = None
+            worst = None
             if kinds[bv] == 2:
-                executed = sign_products(sdp, prec, variants[bv][0], variants[bv][1]) * count / (bms / 1e3) / 1e12
+                worst = sign_products(sdp, prec, variants[bv][0], variants[bv][1]) * count
             res[f"{prec}_s{s}"] = dict(
                 s=s, blocks=count,
                 best_variant=dict(N=variants[bv][0], threads=variants[bv][1],
@@ -954,8 +960,7 @@ def run_projection(args, sdp, torch, stream):
                 default_variant=dict(N=variants[dv][0], threads=variants[dv][1],
                                      method=kind_name[kinds[dv]]),
                 default_ms=times[dv],
-                executed_matrix_tflops=executed,
-                executed_frac_of_peak=None if executed is None else executed / peak,
+                worst_case_matrix_flops=worst,
                 all_variants_ms={vname(v): t for v, t in sorted(times.items())})
             print(f"[bench] projection {prec} s={s}: {count / (bms / 1e3):.3e} proj/s "
                   f"({vname(bv)}, {bms:.3f} ms)", file=sys.stderr, flush=True)
@@ -981,8 +986,7 @@ def run_projection(args, sdp, torch, stream):
         "data": "synthetic",
         "config": {"workload": WORKLOADS["projection"], "headline": "FP32, s = 16"},
         "sizes": res,
-        "roofline": {"kernel": (("k_project_sign16" if head["best_variant"]["N"] == 16
-                                 else "k_project_sign")
+        "roofline": {"kernel": ("k_project_sign_regs"
                                 if head["best_variant"]["method"] == "sign"
                                 else "k_project") + f" (N = {head['best_variant']['N']}, "
                                f"{head['best_variant']['threads']} threads, standalone)",
@@ -991,13 +995,13 @@ def run_projection(args, sdp, torch, stream):
                      "unit": "TFLOP/s", "frac": head["model_frac_of_peak"], "traffic": None,
                      "model": "10 s^3 per block (symmetric eigensolve with vectors 9 s^3, "
                               "rebuild s^3)",
-                     "executed": head["executed_matrix_tflops"],
-                     "executed_frac": head["executed_frac_of_peak"],
-                     "executed_model": "sign method, at most: (3 k1 + 2 k2 + 1) products of the padded "
-                                       "N x N block, 2 N 16^2 flops per 16 x 16 tile; the LDS "
-                                       "kernels form the TN (TN + 1) / 2 tiles on or below the "
-                                       "diagonal (TN = N / 16), the one-wave register kernel "
-                                       "for N = 32 all TN^2; FP32 matrix peak"},
+                     "worst_case_flops": head["worst_case_matrix_flops"],
+                     "worst_case_model": "sign method, a launch whose blocks take every step: "
+                                         "3 (k1 + k2) + 1 products of the padded N x N block, 2 N 16^2 "
+                                         "flops per 16 x 16 tile; the LDS kernels form the "
+                                         "TN (TN + 1) / 2 tiles on or below the diagonal "
+                                         "(TN = N / 16), the one-wave register kernel for N = 32 all "
+                                         "TN^2; these blocks stop after about half"},
         "cpu_baseline": cpu,
     }
     print(json.dumps(line), flush=True)

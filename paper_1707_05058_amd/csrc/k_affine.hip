@@ -265,10 +265,13 @@ __global__ __launch_bounds__(COL_NT) void k_coldot(AffineArgs a) {
 // time: a member that has polled FU_SPIN times computes the missing parts
 // itself, with the same arithmetic, so the results do not depend on it.
 // Bound: HBM; 8 (rows + 2 groups) bytes per column instead of 16 rows.
-// Measured, both products (two passes -> this and k_fused_reduce): 255 MB 75.7
-// -> 45.6 us (one pass at 6.0 TB/s), 769 MB of 12 uneven instances 241 -> 132 us,
-// 339 MB of 8 instances 118 -> 65 us, 101 MB 35 -> 25 us.  Two workgroups of half
-// the columns per unit: 255 MB 47.3 us, 769 MB 142 us.
+// Measured in iterations, both products (two passes -> this + k_fused_reduce):
+// 255 MB 75.7 -> 47.3 + 4.8 us, 769 MB of 12 uneven instances 241 -> 135.8 + 4.8,
+// 101 MB 35 -> 21.8 + 5.3.  The HBM counters give 260, 788 and 103 MB read and 8.7,
+// 9.2 and 7.6 written by this kernel: B is read once, at 5.7, 5.9 and 5.1 TB/s with
+// the sums; what 101 MB lacks is the exchange's latency, not traffic (without it,
+// launched under one tag, 255 MB took 42.4 and 101 MB 19.5 us).  Two workgroups of
+// half the columns per unit: 4% slower at 255 MB, 7% at 769 MB.
 // ---------------------------------------------------------------------------
 constexpr int FU_NT = 512;                 // threads: one workgroup per unit
 constexpr int FU_K = 4;                    // pairs of columns per thread
@@ -276,8 +279,11 @@ constexpr int FU_R = 8;                    // rows at a time
 constexpr int FU_COLS = 2 * FU_NT * FU_K;  // most columns of a member
 constexpr int FU_MAXG = 16;                // most members of a cluster
 constexpr int FU_SPIN = 400;
-// The two passes serve smaller matrices from the L2s (bands: 5.6 MB 10.8 us
-// against 11.2, 15.8 MB 12.9 against 12.7, 31 MB 19.1 against 12.4).
+// The two passes serve smaller matrices from the L2s (bands of 5.6 and 15.8 MB:
+// 10.8 and 12.9 us for both products, in one pass 11.2 and 12.7 even without
+// waiting for the exchange).  Above the line, us per iteration in one pass / two:
+// 21 MB of 11 080 columns 30.9 / 33.2, of 31 880 35.8 / 50.0, of 65 000 48.0 / 80.0,
+// 4 instances of 6 MB 36.0 / 37.3, 40 MB of 11 080 32.9 / 37.7.
 constexpr int64_t FUSED_MIN_BYTES = 20 << 20;
 
 // Sum over each row of 16 lanes, the same in every lane of the row.

@@ -62,7 +62,15 @@ constexpr int DEC_BACK_OFF_SIGN_N = 96;
 // instances (now 220-430).  The probes are the same iterations for every
 // clique of an instance, so that their sweeps coincide; the first, whose sweeps
 // start from the identity (3.5 ms for blocks of 128), pays after some 50
-// decoupled iterations, so a short solve does without.
+// decoupled iterations, so a short solve does without.  Total ms after 50 / 100 /
+// 200 / 500 / 1000 iterations with sweeps and back-off waits, the first probe at
+// 32, and at 64:
+//    40 cliques of 128  44 61 96 191 336 | 20 36 70 160 301 | 17 36 70 156 297
+//   300 of 56           16 31 60 110 193 | 10 19 37  87 171 |  9 18 35  85 170
+//   120 of 76           18 34 64 107 178 |  9 17 34  77 148 |  8 16 30  73 145
+//    10 of 96 (fail)    21 38 71 168 273 |  8 15 41  91 212 |  6 14 34  84 206
+//     3 of 112 (fail)   44 74 101 133 178 | 12 24 46 81 127 |  9 23 44  79 125
+//   45 x 45 grid (fail) 20 36 67 159 312 | 10 21 43 107 214 |  9 20 41 105 211
 struct DecState {
   static constexpr int LONG = 31;
   int64_t it;
@@ -3140,6 +3148,14 @@ hipError_t dispatch_sign(int dtype, int N, int NT, int count, const int32_t *siz
 // A few large FP64 cliques leave most compute units idle with one workgroup
 // per clique: up to SPLIT_MAX_CLIQUES cliques of blocks of 96 or 128 take
 // the split iteration (a block of 128 spreads over 36 waves instead of 8).
+// The line was drawn against k_sign_big without its early stop.  With it, us per
+// iteration of Algorithm 1 (the first 50 / 300-350), split and k_sign_big:
+//   blocks of 96    4 cliques 434 / 434  235 / 264, 40 486 / 488  239 / 217,
+//                  64 617 / 617  250 / 232
+//   blocks of 128   4 cliques 484 / 485  333 / 653, 40 716 / 716  360 / 364,
+//                  64 1044 / 1045  387 / 348
+// so the split form is ahead only where iterates with eigenvalues at 0 take every
+// step in k_sign_big (4 of 128, late: 653).
 constexpr int SPLIT_MAX_CLIQUES = 64;
 
 int64_t split_workspace(int precision, int variant, int count) {
