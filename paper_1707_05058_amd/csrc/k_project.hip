@@ -1621,8 +1621,8 @@ SignPlan sign_plan(double tol, int n) {
   for (int j = 0; j <= 256 * dec; ++j) d.push_back(std::pow(10.0, -dec + j / 256.0));
   for (int j = 1; j <= 1024; ++j) d.push_back(SIGN_X_MAX * j / 1024.0);
   const auto fast = [](double v) { return v * (3.0 - 3.2 * v * v + 1.2 * v * v * v * v); };
-  const auto finish = [](double v, int j) {
-    const SignStep p = sign_finish_step(j);
+  const auto finish = [n](double v, int j) {
+    const SignStep p = sign_finish_step(j, n <= 32);
     const double r = 1.0 - v * v;
     return v * (p.b0 + r * (p.b1 + r * p.b2));
   };
@@ -1908,7 +1908,7 @@ __device__ __forceinline__ void sign_iterate(T (&x)[TB * TB][4], int s, const Si
         n2 = stop;
       }
     } else {
-      p = sign_finish_step(j);
+      p = sign_finish_step(j, true);
       b0 = T(p.b0);
       b1 = T(p.b1);
       b2 = T(p.b2);
@@ -2006,7 +2006,7 @@ __device__ __forceinline__ void sign_iterate_few(T (&x)[TB * TB][4], int s, cons
 #pragma unroll 1
   for (int j = 0; j < stop; ++j) {
     T y[NTL][4], m[NTL][4], z[NTL][4];
-    const SignStep p = sign_finish_step(j);
+    const SignStep p = sign_finish_step(j, true);
     const T b0 = T(p.b0), b1 = T(p.b1), b2 = T(p.b2);
     sign_prod<T, TB>(x, x, y);
 #pragma unroll
@@ -2650,7 +2650,7 @@ __global__ __launch_bounds__(4 * N, (sign_big_waves<T, N>())) void k_sign_big(Pr
           n2 = stop;
         }
       } else {
-        const SignStep p = sign_finish_step(j);
+        const SignStep p = sign_finish_step(j, false);
         b0 = T(p.b0);
         b1 = T(p.b1);
         b2 = T(p.b2);

@@ -161,15 +161,24 @@ constexpr SignStep SIGN_FAST = {SIGN_FAST_1 + SIGN_FAST_3 + SIGN_FAST_5,
                                 -SIGN_FAST_3 - 2.0 * SIGN_FAST_5, SIGN_FAST_5};
 // The finishing steps.  A fast step takes the eigenvalues that ||I - X^2||_F <=
 // 0.9 leaves, [0.316, 1.21], to [0.851, 1.2105]; step 0 is the best uniform
-// approximation of +1 there (within 0.0034), step 1 the third-order step for
-// that range (2.5 ((x - 1)^3 - 3/4 h^2 (x - 1)) about 1: within 2.5e-8), the
-// later ones the third-order step itself (15 x - 10 x^3 + 3 x^5) / 8.  Two of
-// them do for FP32 and three for FP64, 6 and 9 products, where Newton-Schulz
-// steps x (3 - x^2) / 2 took 8 and 10.
-__host__ __device__ inline SignStep sign_finish_step(int j) {
+// approximation of +1 there (within H = 0.0034), step 1 the third-order step for
+// that range, 2.5 ((x - 1)^3 - c H^2 (x - 1)) about 1, the later ones the
+// third-order step itself (15 x - 10 x^3 + 3 x^5) / 8.  Two of them do for FP32
+// and three for FP64, 6 and 9 products, where Newton-Schulz steps x (3 - x^2) / 2
+// took 8 and 10.
+// c = 3/4 has the smallest bound, 2.5e-8, but leaves the eigenvalues that were
+// near +-1 already, which step 0 takes to 1 + 0.6 H, all 2.2e-8 short, and a
+// solve adds that up.  Blocks of up to 32 have room in their tolerance for
+// c = 0.4, bound 5.8e-8, with its zero at 1 + 0.63 H (the steps each tolerance
+// needs are counted with it).  Relative error of X, FP32 against FP64 after 100
+// iterations, all steps of sign_schedule -> c = 3/4 -> c = 0.4: bands of 1985
+// cliques of 16 1.6e-7 -> 2.4e-7 -> 1.6e-7, of 6985 of 16 1.7e-7 -> 2.8e-7 ->
+// 1.6e-7, of 1975 of 26 2.1e-7 -> 2.8e-7 -> 1.9e-7, an arrow of 50 of 24 3.0e-7
+// -> 4.7e-7 -> 1.5e-7, in the same time.
+__host__ __device__ inline SignStep sign_finish_step(int j, bool up_to_32) {
   constexpr double H = 0.00338;
   return j == 0 ? SignStep{1.002014, 0.523437, 0.325222}
-                : SignStep{1.0, j == 1 ? 0.5 + 0.9375 * H * H : 0.5, 0.375};
+                : SignStep{1.0, j == 1 ? 0.5 + 1.25 * (up_to_32 ? 0.4 : 0.75) * H * H : 0.5, 0.375};
 }
 SignPlan sign_plan(double tol, int n);   // cached per (tol, n); thread-safe
 int projection_standalone_variant(int precision, int s);  // sign function where built
